@@ -195,6 +195,7 @@ struct CheckLds {
                             // launch's counter once, at the end of the tile, so that the loop
                             // carries no global atomic whose completion a later wait would see
     int nflagged;           // wavefronts that flagged a line at the current check (0 between checks)
+    int bail;               // the tile's operands do not fit the kernel's number format (split FP32 only)
 };
 
 // Clears the tile's check state; before the tile's first barrier.  Census
@@ -412,8 +413,8 @@ __device__ __forceinline__ Thread opaque_lanes(const Thread& th) {
     return t;
 }
 
-template <class G, int FT, bool INJ>
-__device__ __forceinline__ void check(Acc<G>& acc, CheckLds<G>& s, const LaunchArgs& a, const Thread& th_loop, int t, int kp,
+template <class G, int FT, bool INJ, bool BAIL = false>
+__device__ __forceinline__ bool check(Acc<G>& acc, CheckLds<G>& s, const LaunchArgs& a, const Thread& th_loop, int t, int kp,
                                       float& Rr, float& na2, float& Sc, float& nb2, int fnext, int& flogged) {
     constexpr int MI = G::MI, NI = G::NI, TM = G::TM, TN = G::TN, WM = G::WM, WN = G::WN, NW = G::NW;
     const Thread th = opaque_lanes(th_loop);
@@ -427,6 +428,9 @@ __device__ __forceinline__ void check(Acc<G>& acc, CheckLds<G>& s, const LaunchA
     const float wna = wave_sum(na), wnb = wave_sum(nb);
     if (lane == 0) { s.nsum[0][th.wave] = wna; s.nsum[1][th.wave] = wnb; }
     __syncthreads();
+    if constexpr (BAIL) {
+        if (__builtin_amdgcn_readfirstlane(s.bail)) return true;
+    }
 
     // (3) residuals, thresholds (the analytic FP32 roundoff bound), flags
     float sa = s.nsum[0][0], sb = s.nsum[1][0];
@@ -498,7 +502,7 @@ __device__ __forceinline__ void check(Acc<G>& acc, CheckLds<G>& s, const LaunchA
         flogged = fnext;
     }
     __syncthreads();
-    if (__builtin_amdgcn_readfirstlane(s.nflagged) == 0) return;
+    if (__builtin_amdgcn_readfirstlane(s.nflagged) == 0) return false;
 
     // rare path: something was flagged (uniform branch)
     int nr = 0, ncl = 0, fr = -1, fc = -1;
@@ -616,6 +620,7 @@ __device__ __forceinline__ void check(Acc<G>& acc, CheckLds<G>& s, const LaunchA
         }
         if (th.tid == 0 && (kind == FTGEMM_EV_DETECTED || kind == FTGEMM_EV_UNCORRECTABLE)) s.tainted = 1;
     }
+    return false;
 }
 
 // ---------------------------------------------------------------------------

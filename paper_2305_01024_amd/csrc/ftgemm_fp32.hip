@@ -2,22 +2,36 @@
 // (the tile computation is in ftgemm_fp32.hpp).
 #include <algorithm>
 
-#include "ftgemm_fp32.hpp"
+#include "ftgemm_split.hpp"
 
 namespace ftgemm_impl {
 namespace {
 
-// WAVE: wavefront-tile checks (FT levels only).  The 128 x 128 tile's LDS
-// (79 KB) leaves room for two workgroups per compute unit; asking for two
-// wavefronts per SIMD holds its FT kernels to 256 VGPRs, which they fit in
-// without spilling in the main loop (the plain kernel is there already).
+// WAVE: wavefront-tile checks (FT levels only).  The square compute-tile
+// variants from 128 x 128 run the split kernel (ftgemm_split.hpp).  The
+// 128 x 128 tile's LDS (79 KB) leaves room for two workgroups per compute unit;
+// asking for two wavefronts per SIMD holds its kernels to 256 VGPRs.
+template <int BM, int BN, bool WAVE>
+constexpr bool kSplit = BM == BN && BM >= 128 && !WAVE;
 template <int BM, int BN, int FT>
 constexpr int kMinWaves = (BM == 128 && BN == 128 && FT > 0) ? 2 : 1;
 template <int BM, int BN, int BK, int WM, int WN, int FT, bool INJ, bool WAVE = false>
 __global__ __launch_bounds__(64 * WM * WN, (kMinWaves<BM, BN, FT>)) void ftgemm_f32_kernel(LaunchArgs a) {
-    __shared__ f32::Smem<BM, BN, BK, WM, WN, WAVE> sm;
     const int ntm = (a.M + BM - 1) / BM;
-    f32::tile<BM, BN, BK, WM, WN, FT, INJ, WAVE>(a, blockIdx.x % ntm, blockIdx.x / ntm, sm);
+    const int tm = blockIdx.x % ntm, tn = blockIdx.x / ntm;
+    if constexpr (kSplit<BM, BN, WAVE>) {
+        __shared__ union {
+            f32s::SmemSplit<BM, BN, WM, WN> split;
+            f32::Smem<BM, BN, BK, WM, WN> full;
+        } sm;
+        if (f32s::tile<BM, BN, WM, WN, FT, INJ>(a, tm, tn, sm.split)) return;
+        // operands outside the split's range: the tile again on the FP32 matrix instructions
+        __syncthreads();
+        f32::tile<BM, BN, BK, WM, WN, FT, INJ>(a, tm, tn, sm.full);
+    } else {
+        __shared__ f32::Smem<BM, BN, BK, WM, WN, WAVE> sm;
+        f32::tile<BM, BN, BK, WM, WN, FT, INJ, WAVE>(a, tm, tn, sm);
+    }
 }
 
 // Recomputes the tiles a launch of the same variant queued (FT levels only).

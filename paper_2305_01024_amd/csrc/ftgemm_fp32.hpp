@@ -1,4 +1,7 @@
-// ftgemm_fp32.hpp -- FP32 online ABFT GEMM kernels for gfx950 (MI355X).
+// ftgemm_fp32.hpp -- FP32 online ABFT GEMM kernels for gfx950 (MI355X), on the
+// FP32 matrix instructions: the rectangular and the 64 x 64 tiles, wavefront-tile
+// checks, recomputed tiles, and the tiles whose operands the split kernels
+// (ftgemm_split.hpp) cannot hold.
 //
 // One workgroup (WM x WN wavefronts) computes one BM x BN output tile, which
 // is also the check tile.  The k-loop runs in steps of BK with A/B panels

@@ -1,0 +1,426 @@
+// ftgemm_split.hpp -- FP32 online ABFT GEMM on the bf16 matrix instructions (gfx950).
+//
+// The FP32 matrix instruction takes 64 cycles for 32 x 32 x 2, the bf16 one 32
+// cycles for 32 x 32 x 16: sixteen times the rate.  Every FP32 operand is split
+// exactly into three bf16 parts, x = x0 + x1 + x2 (each the rest rounded to
+// nearest: 8 + 8 + 8 bits), and a product is the six part products down to
+// 2^-16 of the largest, x0 y0, x0 y1, x1 y0, x1 y1, x0 y2 and x2 y0, added to
+// one FP32 accumulator; the dropped ones are below 2^-25 of |x y| and of either
+// sign.  Against 64 bits the result is closer than the FP32 instruction's
+// (2-norm of the error over K = 64 .. 8192 on normal, uniform, positive and
+// heavy-tailed operands: 0.6 to 0.93 of it), because an accumulator is rounded
+// once per 16 k and product instead of once per k.  (Cutting the leading part
+// off instead of rounding it leaves remainders of one sign, and on positive
+// data the small products are then lost to rounding all in one direction.)
+//
+// The fault tolerance is that of the FP32 kernels (ftgemm_fp32.hpp: encodings
+// from the staging registers, references per line, the check of
+// ftgemm_abft.hpp), in FP32 on the unsplit operands.  A thread keeps the four
+// lines x 4 k it stages in registers until the panel's encodings are complete,
+// one barrier later, and adds their products with the encodings to its own
+// partial references, which are summed over the four threads of a line only at
+// a check: the owners' reads of whole rows and columns from LDS are gone.
+//
+// What bounds it: at 256 x 256 and 8192^3 the matrix instructions take 3.1 ms
+// of 5.3 at the 1.9-2.0 GHz the chip then runs at (six times the library's
+// bf16 product of that size takes 5.8 ms).  Vector instructions issue beside
+// matrix instructions of either wavefront on the SIMD (measured: six between
+// two MFMAs are 90-95% hidden; v_dot2 is the exception, it waits for the matrix
+// pipe), so the split, the encodings and the reference updates of a panel,
+// about 190 instructions per wavefront, are dealt out between its 48 MFMAs.
+// 8192^3 online: 8.71 ms on the FP32 instructions, 5.32 ms here; 2048^3 (one
+// 128 x 128 tile per compute unit, bound by the latency of a panel: LDS reads
+// after the barrier, split and store before the next) 0.210 -> 0.150 ms.
+//
+// Where the split does not hold: bits below bf16's smallest denormal (operand
+// elements under 2^-110), and Inf, NaN or norms near overflow.  Both are seen
+// before the first check that would cover them; the tile is then computed
+// again by f32::tile, which is what the kernel's callers do on `false`.
+#pragma once
+
+#include "ftgemm_fp32.hpp"
+
+namespace ftgemm_impl {
+namespace f32s {
+
+using namespace abft;
+
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
+
+constexpr int KC = 16;      // k of one panel (one 32x32x16 MFMA deep)
+constexpr int PARTS = 3;
+
+// A panel in fragment order: [part][block of 32 rows][16-byte unit], 64 units
+// of 8 k per block.  The unit of (row, lane half) is a permutation of the
+// block, so a fragment read is 1 KB of consecutive LDS in some lane order.
+template <int ROWS>
+struct Panel {
+    unsigned short p[PARTS][ROWS / 32][64][8];
+};
+
+// The encodings are kept as the partial sums of the wavefronts that stage a
+// panel; their readers add them.  (LDS float atomics into one sum took 200
+// LDS cycles per wavefront and panel at 256 x 256, more than every other LDS
+// access of the step together.)
+template <int BM, int BN, int NE>   // NE: wavefronts per role
+struct alignas(16) OperandsSplit {
+    Panel<BM> A[2];
+    Panel<BN> B[2];
+    float wsum[2][NE][KC];      // e^T A per k
+    float vsum[2][NE][KC];      // B e per k
+    float dummy[64];            // sink for the stores of lanes that own no value
+};
+
+template <int BM, int BN, int WM, int WN>
+struct SmemSplit {
+    OperandsSplit<BM, BN, WM * WN / 2> op;
+    CheckLds<Geometry<BM, BN, WM, WN>> ck;
+};
+
+// Unit of (row % 32, lane half).  A's stores write rows 4 apart, B's
+// consecutive columns, both for all four k-quads; with these permutations the
+// 16 lanes of a store group fall into 16 distinct bank pairs.
+__device__ __forceinline__ int unit_a(int row, int half) { return (row ^ ((row >> 3) & 3) ^ (half << 1)) + 32 * half; }
+__device__ __forceinline__ int unit_b(int row, int half) { return (row ^ (half << 2)) + 32 * half; }
+
+__device__ __forceinline__ unsigned pack_bf16(float a, float b) {
+    return __builtin_bit_cast(unsigned, __builtin_convertvector(f32x2{a, b}, bf16x2));
+}
+__device__ __forceinline__ float bf_lo(unsigned x) { return __uint_as_float(x << 16); }
+__device__ __forceinline__ float bf_hi(unsigned x) { return __uint_as_float(x & 0xffff0000u); }
+
+// Norm squares from here on may overflow an intermediate sum of the parts.
+constexpr float kHugeNorm2 = 3.3e38f;
+
+// Whether every operand element of the tile can take the split path.
+template <class G>
+__device__ __forceinline__ bool splittable(const LaunchArgs& a, const Thread& th, int* flag) {
+    auto bad = [](float x) {
+        const unsigned u = __float_as_uint(x) & 0x7fffffffu;
+        return (u != 0 && u < 0x0d800000u) || u > 0x5f000000u;   // below 2^-100, above 2^63
+    };
+    bool b = false;
+    for (int64_t x = th.tid; x < (int64_t)th.mI * a.K; x += G::NT)
+        b |= bad(a.A[(x / th.mI) * a.lda + th.i0 + x % th.mI]);
+    for (int64_t x = th.tid; x < (int64_t)th.nJ * a.K; x += G::NT) b |= bad(a.B[(th.j0 + x / a.K) * a.ldb + x % a.K]);
+    if (th.tid == 0) *flag = 0;
+    __syncthreads();
+    if (b) *flag = 1;
+    __syncthreads();
+    const bool ok = __builtin_amdgcn_readfirstlane(*flag) == 0;
+    __syncthreads();
+    return ok;
+}
+
+// One BM x BN tile.  Returns false, with C untouched, when the tile's
+// operands do not fit the split; the caller then runs f32::tile.
+template <int BM, int BN, int WM, int WN, int FT, bool INJ>
+__device__ __forceinline__ bool tile(const LaunchArgs& a, int tm, int tn, SmemSplit<BM, BN, WM, WN>& sm) {
+    using G = Geometry<BM, BN, WM, WN>;
+    constexpr int NT = G::NT, TM = G::TM, TN = G::TN, MI = G::MI, NI = G::NI;
+    constexpr int BK = 32;              // k-step of the interface: two panels
+    constexpr int NE = WM * WN / 2;     // wavefronts per role
+    constexpr int LT = 4;               // lines per thread
+    constexpr int LQ = BM / LT;         // line groups per panel
+    static_assert(BM == BN && NT == 2 * BM && LQ % 32 == 0 && NI == 2, "four lines x 4 k per thread");
+
+    auto& op = sm.op;
+    Thread th = make_thread<G, true>(a, tm, tn);
+    const int tid = th.tid, lane = th.lane, wm = th.wm, wn = th.wn, l32 = th.l32, hh = th.hh;
+    const int mI = th.mI;
+    const int nk = (a.K + BK - 1) / BK;
+    const bool row_role = __builtin_amdgcn_readfirstlane(tid >> 6) < NE;
+
+    // offsets inside a panel have to fit in 31 bits
+    if ((int64_t)(KC + 1) * a.lda * 4 >= (int64_t(1) << 31) || (int64_t)(BN + 1) * a.ldb * 4 >= (int64_t(1) << 31)) return false;
+    if (a.M < LT || a.K < LT) return false;
+
+    // ---- roles: the first half of the threads stages A, the other B; thread
+    // st of a role holds k-quad kq = st % 4 of four lines, rows 4 lq + r of A or
+    // columns lq + LQ r of B, and owns line r = kq of them
+    const int st = row_role ? tid : tid - NT / 2;
+    const int kq = st & 3, lq = st >> 2;
+    th.my_row = row_role ? st : -1;
+    th.my_col = row_role ? -1 : lq + LQ * kq;
+
+    if constexpr (FT > 0) {
+        clear_check(sm.ck, tid);
+    }
+    if (tid == 0) sm.ck.bail = 0;
+    int fnext = 0, flogged = 0;
+    if constexpr (INJ) {
+        if (!splittable<G>(a, th, &sm.ck.bail)) return false;
+        gather_faults<G>(sm.ck, a, th);
+    }
+    __syncthreads();
+
+    // ---- global -> registers: four 16-byte loads, x[e] = rows 4 lq .. + 3 of
+    // k = 4 kq + e of A, or k 4 kq .. + 3 of column lq + LQ e of B.
+    // The loads have no alignment beyond a float's and no branch: what lies
+    // outside the matrix is past the resource's end or given an offset there,
+    // and reads as zero.  A load that would straddle the last row of the tile
+    // or the last k is moved back inside, and fix() shifts what it got.
+    constexpr int kOutside = (int)0x80000000;
+    constexpr int inset = LT;     // the base lies four floats early, so that a moved load's offset is not negative
+    auto moved = [&](int off, int rem) { return rem >= LT ? off : rem > 0 ? off - 4 * (LT - rem) : kOutside; };
+    const int voff = row_role ? moved((4 * kq * (int)a.lda + LT * lq + inset) * 4, mI - LT * lq) : (lq * (int)a.ldb + 4 * kq + inset) * 4;
+    const int64_t pstride = row_role ? KC * a.lda * 4 : KC * 4;
+    const int64_t estride = (row_role ? a.lda : (int64_t)LQ * a.ldb) * 4;
+    const bool whole_n = th.nJ == BN;
+    const char* const base0 = row_role ? reinterpret_cast<const char*>(a.A + th.i0 - inset)
+                                       : reinterpret_cast<const char*>(a.B + (int64_t)th.j0 * a.ldb - inset);
+    const int64_t bytes0 = row_role ? ((int64_t)(a.K - 1) * a.lda + (a.M - th.i0 + inset)) * 4
+                                    : ((int64_t)(a.N - 1 - th.j0) * a.ldb + a.K + inset) * 4;
+    constexpr int kRsrcWord3 = 0x00020000;   // raw 32-bit data format
+    auto load = [&](f32x4 (&x)[4], int p) {
+        const int k0 = p * KC;
+        int vo = voff;
+        if (!row_role && k0 + KC > a.K) vo = moved(voff, a.K - (k0 + 4 * kq));
+        // the end of the resource matters only past the last whole panel and
+        // in B's last column tile
+        int nr[4] = {0x7fffffff, 0x7fffffff, 0x7fffffff, 0x7fffffff};
+        if (!(k0 + KC <= a.K && (row_role || whole_n))) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int64_t left = k0 < a.K ? bytes0 - p * pstride - e * estride : 0;
+                nr[e] = (int)(left < 0 ? 0 : left > 0x7fffffff ? 0x7fffffff : left);
+            }
+        }
+        const char* const at = base0 + p * pstride;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const auto rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(at + e * estride), (short)0, nr[e], kRsrcWord3);
+            x[e] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rs, vo, 0, 0));
+        }
+    };
+    const int shift = (LT - (row_role ? mI : a.K) % LT) % LT;
+    auto fix = [&](f32x4 (&x)[4], int k0) {
+        if (shift == 0 || (!row_role && (k0 >= a.K || k0 + KC <= a.K))) return;
+        const int rem = row_role ? mI - LT * lq : a.K - (k0 + 4 * kq);
+        const bool cut = rem > 0 && rem < LT;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+#pragma unroll
+            for (int by = 1; by < LT; by *= 2)
+                if (shift & by) {
+#pragma unroll
+                    for (int q = 0; q < LT; ++q) {
+                        const float from = q + by < LT ? x[e][q + by < LT ? q + by : 0] : 0.f;
+                        x[e][q] = cut ? from : x[e][q];
+                    }
+                }
+        }
+    };
+
+    // ---- registers -> LDS: y[r][q] = k 4 kq + q of line r
+    float y[LT][4];
+    // Low halves of the third parts before they are rounded to bf16.  A
+    // normal one has at most 8 significant bits, so its low half is 0; where
+    // x is so small (below 2^-110) that its last bits are under bf16's
+    // smallest denormal, they show here.
+    unsigned lost = 0;
+    auto transpose = [&](const f32x4 (&x)[4]) {
+#pragma unroll
+        for (int r = 0; r < LT; ++r)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) y[r][q] = row_role ? x[q][r] : x[r][q];
+    };
+    constexpr int PS = BM / 32 * 64 * 8;   // halves per part
+    constexpr int BUF = PARTS * PS;        // halves per panel
+    const int ua = unit_a((LT * lq) & 31, kq >> 1);
+    unsigned short* const dst0 = (row_role ? &op.A[0].p[0][LT * lq >> 5][ua][0] : &op.B[0].p[0][lq >> 5][unit_b(lq & 31, kq >> 1)][0]) +
+                                 4 * (kq & 1);
+    int doff[LT];   // A: row LT lq + r is unit ua ^ r; B: columns LQ apart are LQ / 32 blocks apart
+#pragma unroll
+    for (int r = 0; r < LT; ++r) doff[r] = row_role ? ((ua ^ r) - ua) * 8 : r * (LQ / 32) * 512;
+    u32x2 part[PARTS];
+    auto split_half = [&](int r, int h) {
+        const float x0 = y[r][2 * h], x1 = y[r][2 * h + 1];
+        part[0][h] = pack_bf16(x0, x1);
+        const float e0 = x0 - bf_lo(part[0][h]), e1 = x1 - bf_hi(part[0][h]);
+        part[1][h] = pack_bf16(e0, e1);
+        const float l0 = e0 - bf_lo(part[1][h]), l1 = e1 - bf_hi(part[1][h]);
+        part[2][h] = pack_bf16(l0, l1);
+        lost |= __float_as_uint(l0) | __float_as_uint(l1);
+        asm volatile("" : "+v"(lost));
+    };
+    auto store_line = [&](int buf, int r) {
+        unsigned short* d = dst0 + buf * BUF + doff[r];
+#pragma unroll
+        for (int s = 0; s < PARTS; ++s) *reinterpret_cast<u32x2*>(d + s * PS) = part[s];
+    };
+    // the lane's store of one encoding partial (lanes that own none: the sink) and its reads
+    float* const enc_out = (lane & 12) == 0 ? (row_role ? &op.wsum[0][0][0] : &op.vsum[0][0][0]) +
+                                                  (row_role ? th.wave : th.wave - NE) * KC + 4 * kq + ((lane >> 4) & 3)
+                                            : &op.dummy[lane];
+    const int enc_slot = (lane & 12) == 0 ? NE * KC : 0;
+    const float* const enc_in = (row_role ? &op.vsum[0][0][0] : &op.wsum[0][0][0]) + 4 * kq;
+    float es[4];
+    auto encode_sum = [&]() {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) es[q] = (y[0][q] + y[1][q]) + (y[2][q] + y[3][q]);
+    };
+    auto encode_add = [&](int slot) {
+        ReduceScatter<4, 5, 2>::run(es, lane);
+        enc_out[slot * enc_slot] = es[0];
+    };
+
+    // ---- reference checksums: partial over the thread's k-quads
+    float R[LT], n2[LT], rebase = 0.f;
+#pragma unroll
+    for (int r = 0; r < LT; ++r) R[r] = n2[r] = 0.f;
+    auto ft_update = [&](f32x4 v, int r) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            R[r] = fmaf(y[r][q], v[q], R[r]);
+            n2[r] = fmaf(y[r][q], y[r][q], n2[r]);
+        }
+        asm volatile("" : "+v"(R[r]), "+v"(n2[r]));   // keeps the update here (it would be sunk to the next step)
+    };
+
+    Acc<G> acc;
+#pragma unroll
+    for (int bi = 0; bi < MI; ++bi)
+#pragma unroll
+        for (int bj = 0; bj < NI; ++bj)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[bi][bj][r] = 0.0f;
+
+    const unsigned short* const fa = &op.A[0].p[0][wm * (TM / 32)][unit_a(l32, hh)][0];
+    const unsigned short* const fb = &op.B[0].p[0][wn * (TN / 32)][unit_b(l32, hh)][0];
+    auto frag = [&](const unsigned short* p) { return __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(p)); };
+
+    constexpr int NX = BM == 128 ? 2 : 1;   // panels in flight from global memory
+    f32x4 xs[NX][4];
+    // panel p (LDS buffer `buf`) on the matrix cores, panel p + 1 to the other buffer
+    auto step = [&](int p, auto parity) {
+        constexpr int buf = decltype(parity)::value;
+        auto& x = xs[NX == 2 ? buf ^ 1 : 0];
+        f32x4 v;
+        if constexpr (FT > 0) {
+            v = *reinterpret_cast<const f32x4*>(enc_in + buf * NE * KC);
+#pragma unroll
+            for (int w = 1; w < NE; ++w) v += *reinterpret_cast<const f32x4*>(enc_in + (buf * NE + w) * KC);
+        }
+        // Fragments: both column blocks', and the row blocks' one at a time;
+        // each register is reloaded for the next row block when its last
+        // product of this one is issued, two or more slots before its next use.
+        bf16x8 b[NI][PARTS], f[PARTS];
+        constexpr int PA[6] = {2, 1, 0, 1, 0, 0}, PB[6] = {0, 1, 2, 0, 1, 0};   // the small products first
+        constexpr int FREED[6] = {2, -1, -1, 1, -1, 0};                         // part last used in slot s
+#pragma unroll
+        for (int s = 0; s < PARTS; ++s) {   // in the order of use
+            f[PARTS - 1 - s] = frag(fa + buf * BUF + (PARTS - 1 - s) * PS);
+#pragma unroll
+            for (int bj = 0; bj < NI; ++bj) b[bj][s] = frag(fb + buf * BUF + s * PS + bj * 512);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        // The vector work of the step in units, dealt out over the MFMAs
+        constexpr int FTU = FT > 0 ? LT : 0, EU = FT > 0 ? 2 : 0, U = FTU + 2 + EU + 2 * LT;
+        auto unit = [&](int u) {
+            if (u < FTU) {
+                ft_update(v, u);
+            } else if (u == FTU) {
+                fix(x, (p + 1) * KC);
+                transpose(x);
+            } else if (u == FTU + 1) {
+                load(x, p + 1 + NX);
+            } else if (u < FTU + 2 + EU) {
+                if (u == FTU + 2) encode_sum();
+                else encode_add(buf ^ 1);
+            } else {
+                const int h = u - FTU - EU - 2;
+                split_half(h >> 1, h & 1);
+                if (h & 1) store_line(buf ^ 1, h >> 1);
+            }
+        };
+        constexpr int S = 6 * MI;                 // slots of NI MFMAs
+        constexpr int U0 = FT > 0 ? LT / 2 : 0;   // units that run while the fragments arrive
+#pragma unroll
+        for (int u = 0; u < U0; ++u) unit(u);
+        if constexpr (U0 > 0) __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int s = 0; s < S; ++s) {
+            const int bi = s / 6, c = s % 6;
+#pragma unroll
+            for (int bj = 0; bj < NI; ++bj)
+                acc[bi][bj] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(b[bj][PB[c]], f[PA[c]], acc[bi][bj], 0, 0, 0);
+            if (FREED[c] >= 0 && bi + 1 < MI) f[FREED[c]] = frag(fa + buf * BUF + FREED[c] * PS + (bi + 1) * 512);
+#pragma unroll
+            for (int u = U0; u < U; ++u)
+                if (u * S < (s + 1) * U && (u * S >= s * U || s == 0)) unit(u);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    };
+
+    // injection hook and online check after k-step t; true: the tile leaves the split path
+    bool checked = false;
+    auto post = [&](int t) -> bool {
+        if constexpr (INJ) inject<G>(acc, sm.ck, a, th, t, fnext);
+        checked = false;
+        if constexpr (FT > 0) {
+            if (((t + 1) % a.check_interval == 0) || (t == nk - 1)) {
+                float rr[LT], nn[LT];
+#pragma unroll
+                for (int r = 0; r < LT; ++r) { rr[r] = R[r]; nn[r] = n2[r]; }
+                ReduceScatter<LT, 1, 0>::run(rr, lane);
+                ReduceScatter<LT, 1, 0>::run(nn, lane);
+                if ((lost & 0xffffu) != 0 || !(nn[0] < kHugeNorm2)) sm.ck.bail = 1;
+                const float r0 = rr[0] + rebase;
+                float ref = r0;
+                if (check<G, FT, INJ, true>(acc, sm.ck, a, th, t, min((t + 1) * BK, a.K), ref, nn[0], ref, nn[0], fnext, flogged))
+                    return true;
+                rebase += ref - r0;
+                checked = true;
+            }
+        }
+        return false;
+    };
+
+    load(xs[0], 0);
+    if constexpr (NX == 2) load(xs[NX - 1], 1);
+    fix(xs[0], 0);
+    transpose(xs[0]);
+    load(xs[0], NX);
+#pragma unroll
+    for (int r = 0; r < LT; ++r) {
+        split_half(r, 0);
+        split_half(r, 1);
+        store_line(0, r);
+    }
+    if constexpr (FT > 0) {
+        encode_sum();
+        encode_add(0);
+    }
+    __syncthreads();
+    for (int t = 0; t < nk; ++t) {
+        step(2 * t, std::integral_constant<int, 0>{});
+        __syncthreads();
+        step(2 * t + 1, std::integral_constant<int, 1>{});
+        if (post(t)) return false;
+        if (!checked) __syncthreads();
+    }
+    if constexpr (FT == 0) {
+        if constexpr (!INJ) {
+            float z = 0.f;   // stays 0 unless an accumulator is Inf or NaN
+#pragma unroll
+            for (int bi = 0; bi < MI; ++bi)
+#pragma unroll
+                for (int bj = 0; bj < NI; ++bj)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) z = fmaf(acc[bi][bj][r], 0.f, z);
+            if ((lost & 0xffffu) != 0 || !(z == 0.f)) sm.ck.bail = 1;
+            __syncthreads();
+            if (__builtin_amdgcn_readfirstlane(sm.ck.bail)) return false;
+        }
+    }
+    finish_tile<G, FT>(acc, sm.ck, a, th, 1.0f);
+    return true;
+}
+
+}  // namespace f32s
+}  // namespace ftgemm_impl
