@@ -129,13 +129,21 @@ __device__ __forceinline__ float bitflip(float v, int bit) {
 // Checksum owners: thread t < BM owns tile row t; the column owners are the
 // next BN threads when there are at least BM + BN threads (SPLIT), else
 // thread t < BN.  With SPLIT the role is wave-uniform.
-template <int BM_, int BN_, int WM_, int WN_>
+// ROT: wavefront (wm, wn) holds its 32 x 32 blocks rotated by wn in rows and by
+// wm in columns, so that its block position 0 is another block in each
+// wavefront of a row (column) of wavefronts, at a compile-time place.
+template <int BM_, int BN_, int WM_, int WN_, bool ROT_ = false>
 struct Geometry {
     static constexpr int BM = BM_, BN = BN_, WM = WM_, WN = WN_;
     static constexpr int NT = 64 * WM * WN, NW = WM * WN;
     static constexpr int TM = BM / WM, TN = BN / WN;
     static constexpr int MI = TM / 32, NI = TN / 32;
     static constexpr bool SPLIT = NT >= BM + BN;
+    // the block at a position of the accumulator array, and the position of a block
+    static __device__ __forceinline__ int row_block(int pos, int wn) { return ROT_ ? (pos + wn) % MI : pos; }
+    static __device__ __forceinline__ int col_block(int pos, int wm) { return ROT_ ? (pos + wm) % NI : pos; }
+    static __device__ __forceinline__ int row_pos(int block, int wn) { return ROT_ ? (block + MI * WN - wn) % MI : block; }
+    static __device__ __forceinline__ int col_pos(int block, int wm) { return ROT_ ? (block + NI * WM - wm) % NI : block; }
     static constexpr int COL0 = SPLIT ? BM : 0;
     static_assert(MI >= 1 && NI >= 1, "each wavefront needs at least one 32 x 32 block");
     static_assert(!SPLIT || BM % 64 == 0, "row owners must fill whole wavefronts");
@@ -283,7 +291,7 @@ __device__ __forceinline__ void inject(Acc<G>& acc, CheckLds<G>& s, const Launch
     while (fnext < s.nf && s.fault[fnext].kstep == t) {
         const ftgemm_fault_t f = s.fault[fnext];
         const int ir = f.row % G::TM, jr = f.col % G::TN;
-        const int fbi = ir / 32, fbj = jr / 32, jj = jr % 32;
+        const int fbi = G::row_pos(ir / 32, th.wn), fbj = G::col_pos(jr / 32, th.wm), jj = jr % 32;
         const int freg = ((jj >> 3) << 2) | (jj & 3);
         const bool own = f.row / G::TM == th.wm && f.col / G::TN == th.wn &&
                          th.lane == ((jj >> 2) & 1) * 32 + (ir % 32);
@@ -366,14 +374,14 @@ __device__ __forceinline__ void tile_sums(const Acc<G>& acc, CheckLds<G>& s, con
         ReduceScatter<16, 4, 0>::run(cs, lane);
         if ((l32 & 1) == 0) {
             const int r = l32 >> 1;
-            s.colpart[wm][wn * TN + 32 * bj + 8 * (r >> 2) + 4 * hh + (r & 3)] = cs[0];
+            s.colpart[wm][wn * TN + 32 * G::col_block(bj, wm) + 8 * (r >> 2) + 4 * hh + (r & 3)] = cs[0];
         }
         __builtin_amdgcn_sched_barrier(0);
     }
 #pragma unroll
     for (int bi = 0; bi < MI; ++bi) {
         const float rs = swap_add<5>(rpart[bi], rpart[bi]);
-        if (hh == 0) s.rowpart[wn][wm * TM + 32 * bi + l32] = rs;
+        if (hh == 0) s.rowpart[wn][wm * TM + 32 * G::row_block(bi, wn) + l32] = rs;
     }
 }
 
@@ -413,9 +421,16 @@ __device__ __forceinline__ Thread opaque_lanes(const Thread& th) {
     return t;
 }
 
-template <class G, int FT, bool INJ, bool BAIL = false>
+// LATE: called after that first barrier, for what the caller left to other
+// threads in LDS before the check (its references); returns true to leave
+// without a check, on a value that is the same for the whole workgroup.
+struct NoLate {
+    __device__ __forceinline__ bool operator()() const { return false; }
+};
+template <class G, int FT, bool INJ, class LATE = NoLate>
 __device__ __forceinline__ bool check(Acc<G>& acc, CheckLds<G>& s, const LaunchArgs& a, const Thread& th_loop, int t, int kp,
-                                      float& Rr, float& na2, float& Sc, float& nb2, int fnext, int& flogged) {
+                                      float& Rr, float& na2, float& Sc, float& nb2, int fnext, int& flogged,
+                                      LATE&& late = LATE{}) {
     constexpr int MI = G::MI, NI = G::NI, TM = G::TM, TN = G::TN, WM = G::WM, WN = G::WN, NW = G::NW;
     const Thread th = opaque_lanes(th_loop);
     const int lane = th.lane, l32 = th.l32, hh = th.hh, wm = th.wm, wn = th.wn;
@@ -428,9 +443,7 @@ __device__ __forceinline__ bool check(Acc<G>& acc, CheckLds<G>& s, const LaunchA
     const float wna = wave_sum(na), wnb = wave_sum(nb);
     if (lane == 0) { s.nsum[0][th.wave] = wna; s.nsum[1][th.wave] = wnb; }
     __syncthreads();
-    if constexpr (BAIL) {
-        if (__builtin_amdgcn_readfirstlane(s.bail)) return true;
-    }
+    if (late()) return true;
 
     // (3) residuals, thresholds (the analytic FP32 roundoff bound), flags
     float sa = s.nsum[0][0], sb = s.nsum[1][0];
@@ -525,9 +538,9 @@ __device__ __forceinline__ bool check(Acc<G>& acc, CheckLds<G>& s, const LaunchA
     // Coordinates of (fr, fc) in the accumulator layout; all but the lane
     // tests are uniform, so the block is picked by scalar branches and the
     // element by per-lane selects.
-    const int fbi = correct ? (fr % TM) / 32 : -1;
+    const int fbi = correct ? G::row_pos((fr % TM) / 32, wn) : -1;
     const int fjr = correct ? fc % TN : 0;
-    const int fbj = fjr / 32, fjj = fjr % 32;
+    const int fbj = G::col_pos(fjr / 32, wm), fjj = fjr % 32;
     const int freg = ((fjj >> 3) << 2) | (fjj & 3);
     const bool row_lane = correct && wm == fr / TM && l32 == (fr & 31);
     const bool own = row_lane && wn == fc / TN && hh == ((fjj >> 2) & 1);
@@ -906,12 +919,12 @@ __device__ __forceinline__ void epilogue(const Acc<G>& acc, const LaunchArgs& a,
     const float alpha = a.alpha * scale;
 #pragma unroll
     for (int bi = 0; bi < G::MI; ++bi) {
-        const int i = th.wm * G::TM + 32 * bi + th.l32;
+        const int i = th.wm * G::TM + 32 * G::row_block(bi, th.wn) + th.l32;
 #pragma unroll
         for (int bj = 0; bj < G::NI; ++bj)
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
-                const int j = th.wn * G::TN + 32 * bj + 8 * (r >> 2) + 4 * th.hh + (r & 3);
+                const int j = th.wn * G::TN + 32 * G::col_block(bj, th.wm) + 8 * (r >> 2) + 4 * th.hh + (r & 3);
                 if (i < th.mI && j < th.nJ) {
                     float* pc = a.C + (size_t)(th.j0 + j) * a.ldc + (th.i0 + i);
                     float v = alpha * acc[bi][bj][r];

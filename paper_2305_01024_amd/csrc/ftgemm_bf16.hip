@@ -1,20 +1,23 @@
 // ftgemm_bf16.hip -- kernel entry points and variant table of the BF16 kernels
-// (the tile computation is in ftgemm_bf16.hpp).
-#include "ftgemm_bf16.hpp"
+// (the tile computation is in ftgemm_bf16m.hpp; recomputed tiles and shapes
+// outside its loads in ftgemm_bf16.hpp).
+#include "ftgemm_bf16m.hpp"
 
 namespace ftgemm_impl {
 namespace {
 
-// The 128 x 128 tile (79 KB of LDS) fits two workgroups per compute unit;
-// asking for two wavefronts per SIMD holds its FT kernels to 256 VGPRs
-// (unbounded they take 284, one wavefront per SIMD).
-template <int BM, int BN, int FT>
-constexpr int kMinWavesBF16 = (BM == 128 && BN == 128 && FT > 0) ? 2 : 1;
+// Two wavefronts per SIMD: one 256 x 256 or two 128 x 128 workgroups (79 KB of
+// LDS) per compute unit, 256 VGPRs.
 template <int BM, int BN, int BK, int WM, int WN, int FT, bool INJ>
-__global__ __launch_bounds__(64 * WM * WN, (kMinWavesBF16<BM, BN, FT>)) void ftgemm_bf16_kernel(LaunchArgs a) {
-    __shared__ bf16::SmemBF16<BM, BN, BK, WM, WN> sm;
+__global__ __launch_bounds__(64 * WM * WN, 2) void ftgemm_bf16_kernel(LaunchArgs a) {
+    __shared__ union {
+        bf16m::SmemBF16M<BM, BN, WM, WN> m;
+        bf16::SmemBF16<BM, BN, BK, WM, WN> v;
+    } sm;
     const int ntm = (a.M + BM - 1) / BM;
-    bf16::tile<BM, BN, BK, WM, WN, FT, INJ>(a, blockIdx.x % ntm, blockIdx.x / ntm, sm);
+    const int tm = blockIdx.x % ntm, tn = blockIdx.x / ntm;
+    if (bf16m::tile<BM, BN, WM, WN, FT, INJ>(a, tm, tn, sm.m)) return;
+    bf16::tile<BM, BN, BK, WM, WN, FT, INJ>(a, tm, tn, sm.v);
 }
 
 // Recomputes the tiles a launch of the same variant queued (FT levels only).

@@ -1,4 +1,5 @@
-// ftgemm_bf16.hpp -- BF16-input online ABFT GEMM kernels for gfx950 (MI355X).
+// ftgemm_bf16.hpp -- BF16-input online ABFT GEMM kernels for gfx950 (MI355X): the
+// recomputed tiles, and the shapes outside the loads of ftgemm_bf16m.hpp.
 //
 // C = alpha * (scale_a * A) (scale_b * B) + beta * C with A, B in bfloat16 and
 // FP32 accumulation on v_mfma_f32_32x32x16_bf16.  The fault tolerance is the

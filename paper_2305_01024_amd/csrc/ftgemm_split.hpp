@@ -372,7 +372,8 @@ __device__ __forceinline__ bool tile(const LaunchArgs& a, int tm, int tn, SmemSp
                 if ((lost & 0xffffu) != 0 || !(nn[0] < kHugeNorm2)) sm.ck.bail = 1;
                 const float r0 = rr[0] + rebase;
                 float ref = r0;
-                if (check<G, FT, INJ, true>(acc, sm.ck, a, th, t, min((t + 1) * BK, a.K), ref, nn[0], ref, nn[0], fnext, flogged))
+                auto left = [&]() { return __builtin_amdgcn_readfirstlane(sm.ck.bail) != 0; };
+                if (check<G, FT, INJ>(acc, sm.ck, a, th, t, min((t + 1) * BK, a.K), ref, nn[0], ref, nn[0], fnext, flogged, left))
                     return true;
                 rebase += ref - r0;
                 checked = true;
