@@ -50,7 +50,7 @@ struct ftgemm_ctx {
     int grid = 0;
     bool plan_fp8 = false;   // the plan has FP8 problems: launch the kernel that holds the FP8 tile
     // cost model of the batched tile variants: multiply-adds per second
-    double batch_rate[kBatchVariants] = {4.0e13, 2.0e13, 1.6e14, 1.7e14};
+    double batch_rate[kBatchVariants] = {6.4e13, 2.7e13, 1.07e14, 1.19e14};
 };
 
 namespace {

@@ -105,9 +105,6 @@ __device__ __forceinline__ void tile(const LaunchArgs& a, int tm, int tn, Smem<B
     const int mI = th.mI, nJ = th.nJ;
     const int nk = (a.K + BK - 1) / BK;
 
-    const bool alignA = ((reinterpret_cast<uintptr_t>(a.A) & 15) == 0) && ((a.lda & 3) == 0);
-    const bool alignB = ((reinterpret_cast<uintptr_t>(a.B) & 15) == 0) && ((a.ldb & 3) == 0);
-
     if constexpr (FT > 0) {
         for (int x = tid; x < 3 * EB * BK; x += NT) (&op.vsum[0][0][0])[x] = 0.f;
         clear_check(sm.ck, tid);
@@ -121,8 +118,8 @@ __device__ __forceinline__ void tile(const LaunchArgs& a, int tm, int tn, Smem<B
     const float* Abase = a.A + th.i0;
     const float* Bbase = a.B + (size_t)th.j0 * a.ldb;
 
-    // Interior panels (whole tile inside C, full k-step, 16-byte aligned columns)
-    // take the all-vector path; this test is uniform across the workgroup.
+    // Interior panels (whole tile inside C, full k-step) take the all-vector path
+    // (a 16-byte buffer load needs a float's alignment only); this test is uniform across the workgroup.
     // Edge panels load element by element from a clamped address and zero what
     // lies outside the matrix, without divergent branches.
     // Interior panels are read with buffer loads: the per-lane byte offset of
@@ -130,8 +127,8 @@ __device__ __forceinline__ void tile(const LaunchArgs& a, int tm, int tn, Smem<B
     // into the (scalar) resource base and the k-column stride into the scalar
     // offset, so the loop spends no vector instructions on addresses.  Used
     // while every offset of a panel fits in 31 bits.
-    const bool bufA = alignA && (int64_t)BK * a.lda * 4 < (int64_t(1) << 31);
-    const bool bufB = alignB && (int64_t)BN * a.ldb * 4 < (int64_t(1) << 31);
+    const bool bufA = (int64_t)BK * a.lda * 4 < (int64_t(1) << 31);
+    const bool bufB = (int64_t)BN * a.ldb * 4 < (int64_t(1) << 31);
     int voffA[NA], voffB[NB];
 #pragma unroll
     for (int r = 0; r < NA; ++r) {
