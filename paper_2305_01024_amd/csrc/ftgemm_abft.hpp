@@ -871,6 +871,7 @@ __device__ void check_wave(Acc<G>& acc, WaveCheckLds<G>& s, const LaunchArgs& a,
 template <class TileFn>
 __device__ __forceinline__ void retry_queue(const LaunchArgs& a, int ntm, TileFn&& tile_fn) {
     const unsigned count = a.retry[0];
+    if (count == 0) return;   // the usual case: nothing to clear either, no fence and no atomic
     for (unsigned q = blockIdx.x; q < count; q += gridDim.x) {
         const int t = a.retry_tiles[q];
         tile_fn(t % ntm, t / ntm);

@@ -49,8 +49,12 @@ struct ftgemm_ctx {
     int n_items = 0;
     int grid = 0;
     bool plan_fp8 = false;   // the plan has FP8 problems: launch the kernel that holds the FP8 tile
-    // cost model of the batched tile variants: multiply-adds per second
-    double batch_rate[kBatchVariants] = {6.4e13, 2.7e13, 1.07e14, 1.19e14};
+    // cost model of the batched tile variants: multiply-adds per second, as
+    // ftgemm_tune_batched measures them (512^3), but for the FP32 64 x 64 tile:
+    // 2.7e13 there, less on sizes that divide by nothing, which it alone still
+    // loads element by element (1024 problems of 32 to 2048: 2.15 ms with 2.7e13,
+    // 2.00 ms with 2.0e13)
+    double batch_rate[kBatchVariants] = {6.4e13, 1.8e13, 1.07e14, 1.19e14};
 };
 
 namespace {

@@ -15,8 +15,8 @@
 // holds the FP8 tile (F8); the others leave it out and keep the register
 // allocation of the FP32 and BF16 paths as it is without it.
 #include "ftgemm_bf16m.hpp"
+#include "ftgemm_fp8m.hpp"
 #include "ftgemm_split.hpp"
-#include "ftgemm_fp8.hpp"
 
 namespace ftgemm_impl {
 namespace {
@@ -31,6 +31,7 @@ union BatchSmem {
     f32::Smem<64, 64, 64, 2, 2> f32_64;
     bf16m::SmemBF16M<128, 128, 2, 2> bf16m_128;
     bf16::SmemBF16<128, 128, 64, 2, 2> bf16_128;
+    std::conditional_t<F8, fp8m::SmemFP8M<128, 128, 2, 2>, NoLds> fp8m_128;
     std::conditional_t<F8, fp8::SmemFP8<128, 128, 64, 2, 2>, NoLds> fp8_128;
 };
 
@@ -101,7 +102,8 @@ __global__ __launch_bounds__(kBatchThreads, 2) void ftgemm_batched_kernel(BatchA
             default:
                 if constexpr (F8) {
                     if (p.variant == 3) {
-                        fp8::tile<128, 128, 64, 2, 2, FT, INJ>(a, tm, tn, sm.fp8_128);
+                        if (!fp8m::tile<128, 128, 2, 2, FT, INJ>(a, tm, tn, sm.fp8m_128))
+                            fp8::tile<128, 128, 64, 2, 2, FT, INJ>(a, tm, tn, sm.fp8_128);
                         break;
                     }
                 }

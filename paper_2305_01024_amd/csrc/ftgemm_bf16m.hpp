@@ -56,7 +56,7 @@ template <int BM, int BN, int NW>
 struct alignas(16) OperandsBF16M {
     unsigned short A[2][BM / 32][SUBS][64][8];
     unsigned short B[2][BN / 32][SUBS][64][8];
-    unsigned short venc[2][SUBS][2][3 * NW][8];
+    unsigned short venc[2][SUBS][2][3 * NW + 1][8];   // (odd row count: a store's eight octets fall into eight bank groups)
     unsigned short wenc[2][SUBS][2][4][8];
     unsigned short zero[8];
     float nrow[8][BM];          // squares of the rows by k-octet, at a check
@@ -247,22 +247,27 @@ __device__ __forceinline__ bool tile(const LaunchArgs& a, int tm, int tn, SmemBF
             asm volatile("" : "+v"(nb[r]));
         }
     };
-    // three bf16 parts of an encoding value, `rows` units apart
-    auto put = [&](unsigned short* d, float v) {
+    // three bf16 parts of an encoding value
+    auto parts = [&](float v, unsigned (&w)[3]) {
 #pragma unroll
         for (int s = 0; s < 3; ++s) {
-            const unsigned w = pack_bf16(v, v);
-            d[8 * s] = (unsigned short)w;
-            v -= bf_lo(w);
+            w[s] = pack_bf16(v, v);
+            v -= bf_lo(w[s]);
         }
     };
     auto put_w = [&](int buf) {   // after the reduce-scatter over the octet's lanes: k = 8 ao + al / (AL / 8)
         const Slot q = slot_of();
-        put(&op.wenc[buf][q.ao >> 1][q.ao & 1][0][q.al / (AL / 8)], ea[0]);
+        const int s = min(q.lane & (AL / 8 - 1), 2);   // each part by a lane of its own
+        unsigned w[3];
+        parts(ea[0], w);
+        op.wenc[buf][q.ao >> 1][q.ao & 1][s][q.al / (AL / 8)] = (unsigned short)(s == 0 ? w[0] : s == 1 ? w[1] : w[2]);
     };
     auto put_v = [&](int buf) {   // k = 8 bo + (lane >> 3)
         const Slot q = slot_of();
-        put(&op.venc[buf][q.bo >> 1][q.bo & 1][3 * wave][q.lane >> 3], eb[0]);
+        unsigned w[3];
+        parts(eb[0], w);
+#pragma unroll
+        for (int s = 0; s < 3; ++s) op.venc[buf][q.bo >> 1][q.bo & 1][3 * wave + s][q.lane >> 3] = (unsigned short)w[s];
     };
 
     Acc<G> acc;
@@ -313,6 +318,7 @@ __device__ __forceinline__ bool tile(const LaunchArgs& a, int tm, int tn, SmemBF
         const int ln = opaque_tid() & 63, c32 = ln & 31, ch = ln >> 5;
         const int u = 8 * unit_a(c32, ch);
         constexpr int S1 = MI + (FT > 0 ? 1 : 0), S = SUBS * S1;   // slots of two MFMAs
+        constexpr int SU = S - 2;                                      // the last ones without vector work
 #pragma unroll
         for (int s = 0; s < SUBS; ++s) {
             const int ub = 8 * unit_b(c32, 2 * s + ch);
@@ -339,7 +345,7 @@ __device__ __forceinline__ bool tile(const LaunchArgs& a, int tm, int tn, SmemBF
                 const int slot = s * S1 + q;
 #pragma unroll
                 for (int v = 0; v < U; ++v)
-                    if (v * S >= slot * U && v * S < (slot + 1) * U) unit(v);
+                    if (v * SU >= slot * U && v * SU < (slot + 1) * U) unit(v);
                 __builtin_amdgcn_sched_barrier(0);
             }
         }

@@ -1,19 +1,22 @@
 // ftgemm_fp8.hip -- kernel entry points and variant table of the FP8 kernels
-// (the tile computation is in ftgemm_fp8.hpp).
-#include "ftgemm_fp8.hpp"
+// (the tile computation is in ftgemm_fp8m.hpp; recomputed tiles and shapes
+// outside its loads in ftgemm_fp8.hpp).
+#include "ftgemm_fp8m.hpp"
 
 namespace ftgemm_impl {
 namespace {
 
-// The 128 x 128 tile (41 KB of LDS) fits several workgroups per compute
-// unit; asking for two wavefronts per SIMD keeps its kernels at 256 VGPRs.
-template <int BM, int BN>
-constexpr int kMinWavesFP8 = (BM == 128 && BN == 128) ? 2 : 1;
+// Two wavefronts per SIMD, 256 VGPRs.
 template <int BM, int BN, int BK, int WM, int WN, int FT, bool INJ>
-__global__ __launch_bounds__(64 * WM * WN, (kMinWavesFP8<BM, BN>)) void ftgemm_fp8_kernel(LaunchArgs a) {
-    __shared__ fp8::SmemFP8<BM, BN, BK, WM, WN> sm;
+__global__ __launch_bounds__(64 * WM * WN, 2) void ftgemm_fp8_kernel(LaunchArgs a) {
+    __shared__ union {
+        fp8m::SmemFP8M<BM, BN, WM, WN> m;
+        fp8::SmemFP8<BM, BN, BK, WM, WN> v;
+    } sm;
     const int ntm = (a.M + BM - 1) / BM;
-    fp8::tile<BM, BN, BK, WM, WN, FT, INJ>(a, blockIdx.x % ntm, blockIdx.x / ntm, sm);
+    const int tm = blockIdx.x % ntm, tn = blockIdx.x / ntm;
+    if (fp8m::tile<BM, BN, WM, WN, FT, INJ>(a, tm, tn, sm.m)) return;
+    fp8::tile<BM, BN, BK, WM, WN, FT, INJ>(a, tm, tn, sm.v);
 }
 
 // Recomputes the tiles a launch of the same variant queued (FT levels only).

@@ -1,4 +1,5 @@
-// ftgemm_fp8.hpp -- FP8 (OCP E4M3) input online ABFT GEMM kernels for gfx950.
+// ftgemm_fp8.hpp -- FP8 (OCP E4M3) input online ABFT GEMM kernels for gfx950: the
+// recomputed tiles, and the shapes outside the loads of ftgemm_fp8m.hpp.
 //
 // C = alpha * (scale_a * A) (scale_b * B) + beta * C with A, B as E4M3 codes
 // and FP32 accumulation on v_mfma_scale_f32_32x32x64_f8f6f4 (unit scales).  The fault tolerance

@@ -1,0 +1,423 @@
+// ftgemm_fp8m.hpp -- FP8 (OCP E4M3) input online ABFT GEMM for gfx950: operands
+// of any alignment, references on the matrix cores.
+//
+// The staging, the encodings and the references are those of ftgemm_bf16m.hpp;
+// the product is one v_mfma_scale_f32_32x32x64_f8f6f4 per block and 64 k.  That
+// instruction sums its products below FP32 precision, so the references do
+// not use it: the wavefront's reference blocks are converted to bf16 in
+// registers (exactly) and go through the bf16 MFMA with the three-part
+// encodings, as there.
+//
+// What bounds it (256 x 256, a 64-k step): the product takes 1024 matrix cycles
+// per SIMD and the references 512; the step takes about 5000 at the issue rate
+// of two wavefronts per SIMD (about 330 vector instructions of each: decoding,
+// sums and squares of 64 codes per thread are 144, the byte transposes 16, the
+// conversions 32).  8192^3 online 1.88 -> 1.46 ms, plain 0.77 -> 0.63 ms (LDS
+// atomics and owners' reads before; the library's product without fault
+// tolerance: 0.41 ms); unaligned operands took element loads.
+#pragma once
+
+#include "ftgemm_bf16m.hpp"
+#include "ftgemm_fp8.hpp"
+
+namespace ftgemm_impl {
+namespace fp8m {
+
+using namespace abft;
+using bf16::bf16x2;
+using bf16::bf16x8;
+using bf16::bf_lo;
+using bf16::u32x2;
+using bf16::u32x4;
+using bf16m::pack_bf16;
+using fp8::decode4;
+typedef int i32x8 __attribute__((ext_vector_type(8)));
+
+constexpr int KC = 64;           // k of one panel, the k-step of the interface
+constexpr int kScaleOne = 127;   // E8M0 block scale 2^0
+
+// Operand panels in fragment order: 2 KB per block of 32 lines, in 16-byte
+// units of 16 k; a fragment is two reads of 1 KB of LDS in some lane order.
+// venc / wenc: as in the BF16 kernels, by k-octet.
+template <int BM, int BN, int NW>
+struct alignas(16) OperandsFP8M {
+    unsigned char A[2][BM / 32][128][16];
+    unsigned char B[2][BN / 32][128][16];
+    unsigned short venc[2][8][3 * NW + 1][8];
+    unsigned short wenc[2][8][4][8];
+    unsigned short zero[8];
+    float nrow[8][BM];          // squares of the rows by k-octet, at a check
+    float ncol[BN];
+    float rref[BM], cref[BN];   // references at a check
+};
+
+template <int BM, int BN, int WM, int WN>
+struct SmemFP8M {
+    OperandsFP8M<BM, BN, WM * WN> op;
+    CheckLds<Geometry<BM, BN, WM, WN, true>> ck;
+};
+
+// Unit of (line % 32, 16-k quarter).  The lanes of a store group write one
+// octet of rows 4 apart (A) or the eight octets of two columns (B).
+__device__ __forceinline__ int unit_a(int line, int quarter) { return (line ^ ((line >> 3) & 3)) + 32 * quarter; }
+__device__ __forceinline__ int unit_b(int line, int quarter) { return (line ^ (2 * quarter)) + 32 * quarter; }
+
+// eight E4M3 codes as bf16, exactly
+__device__ __forceinline__ bf16x8 to_bf16(int lo, int hi) {
+    bf16x8 r;
+    const bf16x2 a = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(lo, 1.0f, false), b = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(lo, 1.0f, true);
+    const bf16x2 c = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(hi, 1.0f, false), d = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(hi, 1.0f, true);
+    r[0] = a[0]; r[1] = a[1]; r[2] = b[0]; r[3] = b[1];
+    r[4] = c[0]; r[5] = c[1]; r[6] = d[0]; r[7] = d[1];
+    return r;
+}
+
+// One BM x BN tile.  Returns false, with C untouched, for shapes its loads do
+// not cover (fewer than 4 rows or 8 k, offsets past 31 bits).
+template <int BM, int BN, int WM, int WN, int FT, bool INJ>
+__device__ __forceinline__ bool tile(const LaunchArgs& a, int tm, int tn, SmemFP8M<BM, BN, WM, WN>& sm) {
+    using G = Geometry<BM, BN, WM, WN, true>;
+    constexpr int NT = G::NT, TM = G::TM, TN = G::TN, MI = G::MI, NI = G::NI, NW = G::NW;
+    constexpr int AL = BM / 4;          // lanes that hold one k-octet of the A panel
+    constexpr int CQ = NT / 8;          // columns per B load
+    static_assert(BM == BN && NT == 2 * BM && (AL == 64 || AL == 32) && 3 * NW <= 24, "four rows and four columns x 8 k per thread");
+    static_assert(MI == WN && NI == WM, "one reference block of rows and one of columns per wavefront");
+
+    auto& op = sm.op;
+    Thread th = make_thread<G, true>(a, tm, tn);
+    const int tid = th.tid, wm = th.wm, wn = th.wn, l32 = th.l32, hh = th.hh;
+    const int mI = th.mI, nJ = th.nJ;
+    const int nk = (a.K + KC - 1) / KC;
+    if ((int64_t)(KC + 1) * a.lda >= (int64_t(1) << 31) || (int64_t)(BN + 1) * a.ldb >= (int64_t(1) << 31)) return false;
+    if (a.M < 4 || a.K < 8) return false;
+
+    // ---- staging: a thread holds rows 4 al .. 4 al + 3 of the eight k of
+    // octet ao (all rows of an octet in one wavefront, so that e^T A needs no
+    // sum across wavefronts), and octet bo of columns bc + CQ r.  These indices
+    // and the LDS addresses made of them are derived from opaque_tid() where
+    // they are used: kept over the k-loop they were spilled at 256 x 256, and
+    // every reload waits for the loads in flight.
+    constexpr int OW = 64 / AL;         // octets per wavefront
+    const int wave = th.wave;
+    struct Slot {
+        int al, ao, bo, bc, lane;
+    };
+    auto slot_of = [&]() {
+        const int t = opaque_tid(), l = t & 63;
+        return Slot{l & (AL - 1), OW * wave + l / AL, l & 7, t >> 3, l};
+    };
+
+    if constexpr (FT > 0) {
+        if (tid < 4) reinterpret_cast<unsigned*>(op.zero)[tid] = 0u;
+        clear_check(sm.ck, tid);
+    }
+    int fnext = 0, flogged = 0;
+    if constexpr (INJ) gather_faults<G>(sm.ck, a, th);
+    __syncthreads();
+
+    // Loads have no alignment beyond an element's.  Elements outside the matrix
+    // are given an offset past the resource's end and read as zero; a load
+    // that would straddle the last row of the tile or the last k is moved back
+    // inside, and what it got is shifted (fix_a, fix_b).
+    const unsigned char* const A = static_cast<const unsigned char*>(static_cast<const void*>(a.A));
+    const unsigned char* const B = static_cast<const unsigned char*>(static_cast<const void*>(a.B));
+    constexpr int kOutside = (int)0x80000000;
+    constexpr int inset = 8;      // the bases lie eight elements early, so that a moved load's offset is not negative
+    const int sA = (int)a.lda, sB = CQ * (int)a.ldb;
+    const unsigned char* const baseA = A + th.i0 - inset + (int64_t)(8 * OW * wave) * sA;
+    const unsigned char* const baseB = B + (int64_t)th.j0 * a.ldb - inset;
+    const int voffB = (tid >> 3) * (int)a.ldb + 8 * (tid & 7) + inset;
+    constexpr int kRsrcWord3 = 0x00020000;   // raw 32-bit data format
+    unsigned ra[8];               // four rows of one k each
+    u32x2 rb[4];                  // eight k of one column each
+    auto load_a = [&](int p) {
+        const int k0 = p * KC;
+        const auto rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<unsigned char*>(baseA + (int64_t)k0 * sA), (short)0, 0x7fffffff, kRsrcWord3);
+        const Slot q = slot_of();
+        const int rem = mI - 4 * q.al;
+        const int vo = rem > 0 ? (q.lane >= AL ? 8 * sA : 0) + 4 * q.al + inset - (rem < 4 ? 4 - rem : 0) : kOutside;
+        if (k0 + KC <= a.K) {
+#pragma unroll
+            for (int e = 0; e < 8; ++e) ra[e] = __builtin_amdgcn_raw_buffer_load_b32(rs, vo, e * sA, 0);
+        } else {
+#pragma unroll
+            for (int e = 0; e < 8; ++e) ra[e] = __builtin_amdgcn_raw_buffer_load_b32(rs, k0 + 8 * q.ao + e < a.K ? vo : kOutside, e * sA, 0);
+        }
+    };
+    auto load_b = [&](int p) {
+        const int k0 = p * KC;
+        const auto rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<unsigned char*>(baseB + k0), (short)0, 0x7fffffff, kRsrcWord3);
+        if (k0 + KC <= a.K && nJ == BN) {
+#pragma unroll
+            for (int r = 0; r < 4; ++r) rb[r] = __builtin_bit_cast(u32x2, __builtin_amdgcn_raw_buffer_load_b64(rs, voffB, r * sB, 0));
+        } else {
+            const Slot q = slot_of();
+            const int rem = a.K - (k0 + 8 * q.bo);
+            const int vo = rem > 0 ? voffB - (rem < 8 ? 8 - rem : 0) : kOutside;
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+                rb[r] = __builtin_bit_cast(u32x2, __builtin_amdgcn_raw_buffer_load_b64(rs, q.bc + CQ * r < nJ ? vo : kOutside, r * sB, 0));
+        }
+    };
+    auto fix_a = [&]() {
+        if ((mI & 3) != 0) {
+            const int rem = mI - 4 * slot_of().al;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) ra[e] = rem > 0 && rem < 4 ? ra[e] >> (8 * (4 - (mI & 3))) : ra[e];
+        }
+    };
+    auto fix_b = [&](int k0) {
+        if ((a.K & 7) != 0 && k0 < a.K && k0 + KC > a.K) {
+            const int rem = a.K - (k0 + 8 * slot_of().bo), s = 8 - (a.K & 7);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const unsigned long long v = __builtin_bit_cast(unsigned long long, rb[r]) >> (8 * s);
+                rb[r] = rem > 0 && rem < 8 ? __builtin_bit_cast(u32x2, v) : rb[r];
+            }
+        }
+    };
+
+    // ---- registers -> LDS, squares and encodings (section 2.2, Eq. 1-2)
+    constexpr int BLK = 2048;                    // bytes per block of 32 lines
+    constexpr int BUF = BM / 32 * BLK;           // bytes per panel
+    // rows 4 al + r are units ua ^ r; columns CQ apart are CQ / 32 blocks apart
+    unsigned char *pa = nullptr, *pb = nullptr;
+    int ua = 0;
+    auto address_a = [&](int buf) {
+        const Slot q = slot_of();
+        ua = unit_a((4 * q.al) & 31, q.ao >> 1);
+        pa = &op.A[buf][q.al >> 3][0][8 * (q.ao & 1)];
+    };
+    auto address_b = [&](int buf) {
+        const Slot q = slot_of();
+        pb = &op.B[buf][q.bc >> 5][unit_b(q.bc & 31, q.bo >> 1)][8 * (q.bo & 1)];
+    };
+    float na[4] = {0.f, 0.f, 0.f, 0.f}, nb[4] = {0.f, 0.f, 0.f, 0.f};
+    float ea[8], eb[8];
+    u32x2 y[4];
+    auto transpose = [&](int h) {   // k 4 h .. + 3 of the four rows: a 4 x 4 byte transpose
+        const unsigned t0 = __builtin_amdgcn_perm(ra[4 * h + 1], ra[4 * h], 0x05010400u), t1 = __builtin_amdgcn_perm(ra[4 * h + 1], ra[4 * h], 0x07030602u);
+        const unsigned t2 = __builtin_amdgcn_perm(ra[4 * h + 3], ra[4 * h + 2], 0x05010400u), t3 = __builtin_amdgcn_perm(ra[4 * h + 3], ra[4 * h + 2], 0x07030602u);
+        y[0][h] = __builtin_amdgcn_perm(t2, t0, 0x05040100u);
+        y[1][h] = __builtin_amdgcn_perm(t2, t0, 0x07060302u);
+        y[2][h] = __builtin_amdgcn_perm(t3, t1, 0x05040100u);
+        y[3][h] = __builtin_amdgcn_perm(t3, t1, 0x07060302u);
+    };
+    auto row = [&](int r) { *reinterpret_cast<u32x2*>(pa + 16 * (ua ^ r)) = y[r]; };
+    auto sum_a = [&](int quarter) {   // two of the eight k, from the row quads as loaded
+#pragma unroll
+        for (int e = 2 * quarter; e < 2 * quarter + 2; ++e) {
+            float x[4];
+            decode4(ra[e], x);
+            ea[e] = (x[0] + x[1]) + (x[2] + x[3]);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) na[r] = fmaf(x[r], x[r], na[r]);
+        }
+        asm volatile("" : "+v"(na[0]), "+v"(na[1]), "+v"(na[2]), "+v"(na[3]));
+    };
+    auto column = [&](int r, int half) {
+        if (half == 0) *reinterpret_cast<u32x2*>(pb + r * (CQ / 32) * BLK) = rb[r];
+        if constexpr (FT > 0) {
+            float x[4];
+            decode4(rb[r][half], x);
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                eb[4 * half + q] = r == 0 ? x[q] : eb[4 * half + q] + x[q];
+                nb[r] = fmaf(x[q], x[q], nb[r]);
+            }
+            asm volatile("" : "+v"(nb[r]));
+        }
+    };
+    // three bf16 parts of an encoding value
+    auto parts = [&](float v, unsigned (&w)[3]) {
+#pragma unroll
+        for (int s = 0; s < 3; ++s) {
+            w[s] = pack_bf16(v, v);
+            v -= bf_lo(w[s]);
+        }
+    };
+    auto put_w = [&](int buf) {   // after the reduce-scatter over the octet's lanes: k = 8 ao + al / (AL / 8)
+        const Slot q = slot_of();
+        const int s = min(q.lane & (AL / 8 - 1), 2);   // each part by a lane of its own
+        unsigned w[3];
+        parts(ea[0], w);
+        op.wenc[buf][q.ao][s][q.al / (AL / 8)] = (unsigned short)(s == 0 ? w[0] : s == 1 ? w[1] : w[2]);
+    };
+    auto put_v = [&](int buf) {   // k = 8 bo + (lane >> 3)
+        const Slot q = slot_of();
+        unsigned w[3];
+        parts(eb[0], w);
+#pragma unroll
+        for (int s = 0; s < 3; ++s) op.venc[buf][q.bo][3 * wave + s][q.lane >> 3] = (unsigned short)w[s];
+    };
+
+    Acc<G> acc;
+#pragma unroll
+    for (int bi = 0; bi < MI; ++bi)
+#pragma unroll
+        for (int bj = 0; bj < NI; ++bj)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[bi][bj][r] = 0.0f;
+    // References (Eq. 4) of row block wn and column block wm of the wave tile,
+    // its blocks 0: the MFMA of an encoding fragment with the block's operand
+    // fragment leaves line l % 32 in lane l and, over the registers and lane
+    // halves, one partial sum per encoding row: rows 0-23 (registers 0-11) for
+    // the rows of A, rows 24-26 (registers 12-15) for the columns of B.
+    f32x16 E;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) E[r] = 0.f;
+    float rebase = 0.f;
+
+    const unsigned char* const fa = &op.A[0][wm * (TM / 32)][0][0];
+    const unsigned char* const fb = &op.B[0][wn * (TN / 32)][0][0];
+    auto frag = [&](const unsigned char* p, const unsigned char* q) {
+        const u32x4 lo = *reinterpret_cast<const u32x4*>(p), hi = *reinterpret_cast<const u32x4*>(q);
+        return i32x8{(int)lo[0], (int)lo[1], (int)lo[2], (int)lo[3], (int)hi[0], (int)hi[1], (int)hi[2], (int)hi[3]};
+    };
+
+    auto step = [&](int p, auto parity) {
+        constexpr int buf = decltype(parity)::value, nxt = buf ^ 1;
+        const int ln = opaque_tid() & 63, c32 = ln & 31, ch = ln >> 5;
+        // the vector work of the step in units, dealt out over the MFMAs
+        constexpr int U = FT > 0 ? 24 : 14;
+        auto unit = [&](int u) {
+            if constexpr (FT > 0) {
+                if (u < 4) { if (u == 0) fix_a(); sum_a(u); }
+                else if (u < 6) transpose(u - 4);
+                else if (u == 6) { address_a(nxt); row(0); row(1); }
+                else if (u == 7) { row(2); row(3); }
+                else if (u == 8) load_a(p + 2);
+                else if (u == 9) ReduceScatter<8, ilog2(AL) - 1, 0>::run(ea, opaque_tid() & 63);
+                else if (u == 10) put_w(nxt);
+                else if (u < 19) { if (u == 11) { fix_b((p + 1) * KC); address_b(nxt); } column((u - 11) >> 1, (u - 11) & 1); }
+                else if (u == 19) load_b(p + 2);
+                else if (u == 20) ReduceScatter<8, 5, 3>::run(eb, opaque_tid() & 63);
+                else if (u == 21) put_v(nxt);
+            } else {
+                if (u == 0) { fix_a(); address_a(nxt); }
+                else if (u < 3) transpose(u - 1);
+                else if (u < 7) row(u - 3);
+                else if (u == 7) load_a(p + 2);
+                else if (u == 8) { fix_b((p + 1) * KC); address_b(nxt); }
+                else if (u < 13) column(u - 9, 0);
+                else load_b(p + 2);
+            }
+        };
+        const int u0 = 16 * unit_a(c32, 2 * ch), b0 = 16 * unit_b(c32, 2 * ch), b1 = 16 * unit_b(c32, 2 * ch + 1);
+        auto row_frag = [&](int pos) {
+            const unsigned char* q = fa + buf * BUF + G::row_block(pos, wn) * BLK + u0;
+            return frag(q, q + 512);
+        };
+        auto col_frag = [&](int pos) {
+            const unsigned char* q = fb + buf * BUF + G::col_block(pos, wm) * BLK;
+            return frag(q + b0, q + b1);
+        };
+        i32x8 b[NI], f[2];
+        f[0] = row_frag(0);
+#pragma unroll
+        for (int bj = 0; bj < NI; ++bj) b[bj] = col_frag(bj);
+        __builtin_amdgcn_sched_barrier(0);
+        // slots: the row blocks' MFMAs, and per 16 k the references' two
+        constexpr int RS = FT > 0 ? 4 : 0, S = MI + RS;
+#pragma unroll
+        for (int q = 0; q < S; ++q) {
+            if (q < RS) {   // references first: block 0 of the rows and of the columns, in bf16
+                const bf16x8 ve = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(c32 < 3 * NW ? &op.venc[buf][4 * ch + q][c32][0] : op.zero));
+                const bf16x8 we = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(c32 >= 24 && c32 < 27 ? &op.wenc[buf][4 * ch + q][c32 - 24][0] : op.zero));
+                E = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ve, to_bf16(f[0][2 * q], f[0][2 * q + 1]), E, 0, 0, 0);
+                E = __builtin_amdgcn_mfma_f32_32x32x16_bf16(we, to_bf16(b[0][2 * q], b[0][2 * q + 1]), E, 0, 0, 0);
+            } else {
+                const int bi = q - RS;
+                if (bi + 1 < MI) f[(bi + 1) & 1] = row_frag(bi + 1);
+#pragma unroll
+                for (int bj = 0; bj < NI; ++bj)
+                    acc[bi < 0 ? 0 : bi][bj] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(b[bj], f[bi & 1], acc[bi < 0 ? 0 : bi][bj], 0, 0, 0, kScaleOne, 0, kScaleOne);
+            }
+#pragma unroll
+            for (int v = 0; v < U; ++v)
+                if (v * S >= q * U && v * S < (q + 1) * U) unit(v);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    };
+    auto due = [&](int t) { return FT > 0 && (((t + 1) % a.check_interval == 0) || (t == nk - 1)); };
+    // the squares over the k prefix of step t, before the step stages the next panel
+    auto put_norms = [&]() {
+        const int t = opaque_tid();
+        *reinterpret_cast<f32x4*>(&op.nrow[t / AL][4 * (t & (AL - 1))]) = f32x4{na[0], na[1], na[2], na[3]};
+        float nn[4] = {nb[0], nb[1], nb[2], nb[3]};
+        ReduceScatter<4, 2, 0>::run(nn, t & 63);
+        op.ncol[(t >> 3) + CQ * ((t >> 1) & 3)] = nn[0];
+    };
+    auto post = [&](int t) -> bool {
+        if constexpr (INJ) inject<G>(acc, sm.ck, a, th, t, fnext);
+        if constexpr (FT > 0) {
+            if (due(t)) {
+                float r = ((E[0] + E[1]) + (E[2] + E[3])) + ((E[4] + E[5]) + (E[6] + E[7])) + ((E[8] + E[9]) + (E[10] + E[11]));
+                float c = (E[12] + E[13]) + (E[14] + E[15]);
+                r = swap_add<5>(r, r);
+                c = swap_add<5>(c, c);
+                if (hh == 0) {
+                    op.rref[wm * TM + 32 * wn + l32] = r;
+                    op.cref[wn * TN + 32 * wm + l32] = c;
+                }
+                __syncthreads();
+                float n = 0.f, r0;
+                if (th.row_role) {   // threads 0 .. BM - 1 own the rows, the others the columns
+#pragma unroll
+                    for (int o = 0; o < 8; ++o) n += op.nrow[o][tid];
+                    r0 = op.rref[tid] + rebase;
+                } else {
+                    n = op.ncol[tid - BM];
+                    r0 = op.cref[tid - BM] + rebase;
+                }
+                float ref = r0;
+                check<G, FT, INJ>(acc, sm.ck, a, th, t, min((t + 1) * KC, a.K), ref, n, ref, n, fnext, flogged);
+                rebase += ref - r0;
+                return true;
+            }
+        }
+        return false;
+    };
+
+    load_a(0);
+    load_b(0);
+    fix_a();
+    fix_b(0);
+    if constexpr (FT > 0) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) sum_a(q);
+    }
+    address_a(0);
+    address_b(0);
+    transpose(0);
+    transpose(1);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        row(r);
+        column(r, 0);
+        if constexpr (FT > 0) column(r, 1);
+    }
+    load_a(1);
+    load_b(1);
+    if constexpr (FT > 0) {
+        ReduceScatter<8, ilog2(AL) - 1, 0>::run(ea, opaque_tid() & 63);
+        put_w(0);
+        ReduceScatter<8, 5, 3>::run(eb, opaque_tid() & 63);
+        put_v(0);
+    }
+    __syncthreads();
+    auto advance = [&](int t, auto parity) {
+        if (due(t)) put_norms();
+        step(t, parity);
+        if (!post(t)) __syncthreads();
+    };
+    for (int t = 0; t < nk; t += 2) {
+        advance(t, std::integral_constant<int, 0>{});
+        if (t + 1 < nk) advance(t + 1, std::integral_constant<int, 1>{});
+    }
+    finish_tile<G, FT>(acc, sm.ck, a, th, a.scale);
+    return true;
+}
+
+}  // namespace fp8m
+}  // namespace ftgemm_impl
