@@ -61,8 +61,8 @@ constexpr Variant kVariantsBF16[] = {
 };
 // default-selection cost model (aligned with kVariantsBF16; MI355X, 8192^3)
 constexpr VariantModel kModelsBF16[] = {
-    {1, 8, 994.0f, 505.0f},
-    {2, 4, 786.0f, 337.0f},
+    {1, 8, 1088.0f, 640.0f},
+    {2, 4, 759.0f, 422.0f},
 };
 
 }  // namespace

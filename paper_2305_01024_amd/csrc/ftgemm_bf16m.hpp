@@ -58,7 +58,7 @@ struct alignas(16) OperandsBF16M {
     unsigned short B[2][BN / 32][SUBS][64][8];
     unsigned short venc[2][SUBS][2][3 * NW + 1][8];   // (odd row count: a store's eight octets fall into eight bank groups)
     unsigned short wenc[2][SUBS][2][4][8];
-    unsigned short zero[8];
+    unsigned short zero[SUBS][2][3 * NW + 1][8];    // read in place of the rows a fragment does not have, at venc's offsets
     float nrow[8][BM];          // squares of the rows by k-octet, at a check
     float ncol[BN];
     float rref[BM], cref[BN];   // references at a check
@@ -115,7 +115,7 @@ __device__ __forceinline__ bool tile(const LaunchArgs& a, int tm, int tn, SmemBF
     };
 
     if constexpr (FT > 0) {
-        if (tid < 4) reinterpret_cast<unsigned*>(op.zero)[tid] = 0u;
+        for (int x = tid; x < (int)sizeof(op.zero) / 4; x += NT) reinterpret_cast<unsigned*>(&op.zero[0][0][0][0])[x] = 0u;
         clear_check(sm.ck, tid);
     }
     int fnext = 0, flogged = 0;
@@ -143,29 +143,23 @@ __device__ __forceinline__ bool tile(const LaunchArgs& a, int tm, int tn, SmemBF
         const Slot q = slot_of();
         const int rem = mI - 4 * q.al;
         const int vo = rem > 0 ? (q.lane >= AL ? 8 * sA : 0) + (4 * q.al + inset - (rem < 4 ? 4 - rem : 0)) * 2 : kOutside;
-        if (k0 + KC <= a.K) {
+        const int left = a.K - (k0 + 8 * (AL == 64 ? wave : q.ao));   // (uniform where a wavefront has one octet)
 #pragma unroll
-            for (int e = 0; e < 8; ++e) ra[e] = __builtin_bit_cast(u32x2, __builtin_amdgcn_raw_buffer_load_b64(rs, vo, e * sA, 0));
-        } else {
-#pragma unroll
-            for (int e = 0; e < 8; ++e)
-                ra[e] = __builtin_bit_cast(u32x2, __builtin_amdgcn_raw_buffer_load_b64(rs, k0 + 8 * q.ao + e < a.K ? vo : kOutside, e * sA, 0));
-        }
+        for (int e = 0; e < 8; ++e) ra[e] = __builtin_bit_cast(u32x2, __builtin_amdgcn_raw_buffer_load_b64(rs, e < left ? vo : kOutside, e * sA, 0));
     };
     auto load_b = [&](int p) {
         const int k0 = p * KC;
         const auto rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(baseB + (int64_t)k0 * 2), (short)0, 0x7fffffff, kRsrcWord3);
-        if (k0 + KC <= a.K && nJ == BN) {
-#pragma unroll
-            for (int r = 0; r < 4; ++r) rb[r] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rs, voffB, r * sB, 0));
-        } else {
+        int vo[4] = {voffB, voffB, voffB, voffB};
+        if (!(k0 + KC <= a.K && nJ == BN)) {   // (no loads inside a branch: the waits for them were coarser)
             const Slot q = slot_of();
             const int rem = a.K - (k0 + 8 * q.bo);
-            const int vo = rem > 0 ? voffB - (rem < 8 ? 8 - rem : 0) * 2 : kOutside;
+            const int vk = rem > 0 ? voffB - (rem < 8 ? 8 - rem : 0) * 2 : kOutside;
 #pragma unroll
-            for (int r = 0; r < 4; ++r)
-                rb[r] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rs, q.bc + CQ * r < nJ ? vo : kOutside, r * sB, 0));
+            for (int r = 0; r < 4; ++r) vo[r] = q.bc + CQ * r < nJ ? vk : kOutside;
         }
+#pragma unroll
+        for (int r = 0; r < 4; ++r) rb[r] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rs, vo[r], r * sB, 0));
     };
     auto fix_a = [&]() {
         if ((mI & 3) != 0) {
@@ -317,6 +311,8 @@ __device__ __forceinline__ bool tile(const LaunchArgs& a, int tm, int tn, SmemBF
         };
         const int ln = opaque_tid() & 63, c32 = ln & 31, ch = ln >> 5;
         const int u = 8 * unit_a(c32, ch);
+        const unsigned short* const pv = c32 < 3 * NW ? &op.venc[buf][0][ch][c32][0] : &op.zero[0][0][0][0];
+        const unsigned short* const pw = c32 >= 24 && c32 < 27 ? &op.wenc[buf][0][ch][c32 - 24][0] : &op.zero[0][0][0][0];
         constexpr int S1 = MI + (FT > 0 ? 1 : 0), S = SUBS * S1;   // slots of two MFMAs
         constexpr int SU = S - 2;                                      // the last ones without vector work
 #pragma unroll
@@ -325,10 +321,10 @@ __device__ __forceinline__ bool tile(const LaunchArgs& a, int tm, int tn, SmemBF
             bf16x8 b[NI], f[2], ve = {}, we = {};
             auto row_frag = [&](int pos) { return frag(fa + buf * BUF + G::row_block(pos, wn) * BLK + s * 512 + u); };
             f[0] = row_frag(0);
-            if constexpr (FT > 0) ve = frag(c32 < 3 * NW ? &op.venc[buf][s][ch][c32][0] : op.zero);
+            if constexpr (FT > 0) ve = frag(pv + s * (2 * (3 * NW + 1) * 8));
 #pragma unroll
             for (int bj = 0; bj < NI; ++bj) b[bj] = frag(fb + buf * BUF + G::col_block(bj, wm) * BLK + s * 512 + ub);
-            if constexpr (FT > 0) we = frag(c32 >= 24 && c32 < 27 ? &op.wenc[buf][s][ch][c32 - 24][0] : op.zero);
+            if constexpr (FT > 0) we = frag(pw + s * (2 * 4 * 8));
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int q = 0; q < S1; ++q) {
@@ -350,7 +346,10 @@ __device__ __forceinline__ bool tile(const LaunchArgs& a, int tm, int tn, SmemBF
             }
         }
     };
-    auto due = [&](int t) { return FT > 0 && (((t + 1) % a.check_interval == 0) || (t == nk - 1)); };
+    // the next step with a check (a counter: the remainder of t by a run-time
+    // interval is some forty instructions)
+    int next_check = a.check_interval >= nk ? nk - 1 : a.check_interval - 1;
+    auto due = [&](int t) { return FT > 0 && t == next_check; };
     // the squares over the k prefix of step t, before the step stages the next panel
     auto put_norms = [&]() {
         const int t = opaque_tid();
@@ -384,6 +383,7 @@ __device__ __forceinline__ bool tile(const LaunchArgs& a, int tm, int tn, SmemBF
                 float ref = r0;
                 check<G, FT, INJ>(acc, sm.ck, a, th, t, min((t + 1) * KC, a.K), ref, n, ref, n, fnext, flogged);
                 rebase += ref - r0;
+                next_check = nk - 1 - next_check > a.check_interval ? next_check + a.check_interval : nk - 1;
                 return true;
             }
         }

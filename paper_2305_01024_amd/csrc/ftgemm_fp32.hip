@@ -75,8 +75,8 @@ constexpr Variant kVariants[] = {
 constexpr int kNumVariants = sizeof(kVariants) / sizeof(kVariants[0]);
 // aligned with kVariants (the wavefront-check variant is never auto-selected)
 constexpr VariantModel kModels[] = {
-    {1, 8, 137.4f, 123.3f}, {1, 4, 117.4f, 99.1f}, {1, 4, 118.4f, 95.8f}, {2, 4, 137.0f, 113.1f},
-    {4, 1, 111.1f, 81.9f}, {2, 4, 137.0f, 96.2f},
+    {1, 8, 224.0f, 210.5f}, {1, 4, 123.0f, 105.5f}, {1, 4, 124.0f, 101.0f}, {2, 4, 186.0f, 159.0f},
+    {4, 1, 115.0f, 83.7f}, {2, 4, 186.0f, 96.2f},
 };
 static_assert(sizeof(kModels) / sizeof(kModels[0]) == kNumVariants, "one model entry per variant");
 

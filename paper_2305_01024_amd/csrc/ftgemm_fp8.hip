@@ -60,8 +60,8 @@ constexpr Variant kVariantsFP8[] = {
 };
 // default-selection cost model (aligned with kVariantsFP8; MI355X, 8192^3 rates in TFLOP/s)
 constexpr VariantModel kModelsFP8[] = {
-    {1, 8, 1410.0f, 512.0f},
-    {2, 4, 919.0f, 336.0f},
+    {1, 8, 1782.0f, 770.0f},
+    {2, 4, 1464.0f, 530.0f},
 };
 
 }  // namespace

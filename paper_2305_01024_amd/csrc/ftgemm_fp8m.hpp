@@ -45,7 +45,7 @@ struct alignas(16) OperandsFP8M {
     unsigned char B[2][BN / 32][128][16];
     unsigned short venc[2][8][3 * NW + 1][8];
     unsigned short wenc[2][8][4][8];
-    unsigned short zero[8];
+    unsigned short zero[4][3 * NW + 1][8];    // read in place of the rows a fragment does not have, at venc's offsets
     float nrow[8][BM];          // squares of the rows by k-octet, at a check
     float ncol[BN];
     float rref[BM], cref[BN];   // references at a check
@@ -108,7 +108,7 @@ __device__ __forceinline__ bool tile(const LaunchArgs& a, int tm, int tn, SmemFP
     };
 
     if constexpr (FT > 0) {
-        if (tid < 4) reinterpret_cast<unsigned*>(op.zero)[tid] = 0u;
+        for (int x = tid; x < (int)sizeof(op.zero) / 4; x += NT) reinterpret_cast<unsigned*>(&op.zero[0][0][0])[x] = 0u;
         clear_check(sm.ck, tid);
     }
     int fnext = 0, flogged = 0;
@@ -136,28 +136,23 @@ __device__ __forceinline__ bool tile(const LaunchArgs& a, int tm, int tn, SmemFP
         const Slot q = slot_of();
         const int rem = mI - 4 * q.al;
         const int vo = rem > 0 ? (q.lane >= AL ? 8 * sA : 0) + 4 * q.al + inset - (rem < 4 ? 4 - rem : 0) : kOutside;
-        if (k0 + KC <= a.K) {
+        const int left = a.K - (k0 + 8 * (AL == 64 ? wave : q.ao));   // (uniform where a wavefront has one octet)
 #pragma unroll
-            for (int e = 0; e < 8; ++e) ra[e] = __builtin_amdgcn_raw_buffer_load_b32(rs, vo, e * sA, 0);
-        } else {
-#pragma unroll
-            for (int e = 0; e < 8; ++e) ra[e] = __builtin_amdgcn_raw_buffer_load_b32(rs, k0 + 8 * q.ao + e < a.K ? vo : kOutside, e * sA, 0);
-        }
+        for (int e = 0; e < 8; ++e) ra[e] = __builtin_amdgcn_raw_buffer_load_b32(rs, e < left ? vo : kOutside, e * sA, 0);
     };
     auto load_b = [&](int p) {
         const int k0 = p * KC;
         const auto rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<unsigned char*>(baseB + k0), (short)0, 0x7fffffff, kRsrcWord3);
-        if (k0 + KC <= a.K && nJ == BN) {
-#pragma unroll
-            for (int r = 0; r < 4; ++r) rb[r] = __builtin_bit_cast(u32x2, __builtin_amdgcn_raw_buffer_load_b64(rs, voffB, r * sB, 0));
-        } else {
+        int vo[4] = {voffB, voffB, voffB, voffB};
+        if (!(k0 + KC <= a.K && nJ == BN)) {   // (no loads inside a branch: the waits for them were coarser)
             const Slot q = slot_of();
             const int rem = a.K - (k0 + 8 * q.bo);
-            const int vo = rem > 0 ? voffB - (rem < 8 ? 8 - rem : 0) : kOutside;
+            const int vk = rem > 0 ? voffB - (rem < 8 ? 8 - rem : 0) : kOutside;
 #pragma unroll
-            for (int r = 0; r < 4; ++r)
-                rb[r] = __builtin_bit_cast(u32x2, __builtin_amdgcn_raw_buffer_load_b64(rs, q.bc + CQ * r < nJ ? vo : kOutside, r * sB, 0));
+            for (int r = 0; r < 4; ++r) vo[r] = q.bc + CQ * r < nJ ? vk : kOutside;
         }
+#pragma unroll
+        for (int r = 0; r < 4; ++r) rb[r] = __builtin_bit_cast(u32x2, __builtin_amdgcn_raw_buffer_load_b64(rs, vo[r], r * sB, 0));
     };
     auto fix_a = [&]() {
         if ((mI & 3) != 0) {
@@ -303,6 +298,8 @@ __device__ __forceinline__ bool tile(const LaunchArgs& a, int tm, int tn, SmemFP
                 else load_b(p + 2);
             }
         };
+        const unsigned short* const pv = c32 < 3 * NW ? &op.venc[buf][4 * ch][c32][0] : &op.zero[0][0][0];
+        const unsigned short* const pw = c32 >= 24 && c32 < 27 ? &op.wenc[buf][4 * ch][c32 - 24][0] : &op.zero[0][0][0];
         const int u0 = 16 * unit_a(c32, 2 * ch), b0 = 16 * unit_b(c32, 2 * ch), b1 = 16 * unit_b(c32, 2 * ch + 1);
         auto row_frag = [&](int pos) {
             const unsigned char* q = fa + buf * BUF + G::row_block(pos, wn) * BLK + u0;
@@ -322,8 +319,8 @@ __device__ __forceinline__ bool tile(const LaunchArgs& a, int tm, int tn, SmemFP
 #pragma unroll
         for (int q = 0; q < S; ++q) {
             if (q < RS) {   // references first: block 0 of the rows and of the columns, in bf16
-                const bf16x8 ve = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(c32 < 3 * NW ? &op.venc[buf][4 * ch + q][c32][0] : op.zero));
-                const bf16x8 we = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(c32 >= 24 && c32 < 27 ? &op.wenc[buf][4 * ch + q][c32 - 24][0] : op.zero));
+                const bf16x8 ve = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(pv + q * ((3 * NW + 1) * 8)));
+                const bf16x8 we = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(pw + q * (4 * 8)));
                 E = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ve, to_bf16(f[0][2 * q], f[0][2 * q + 1]), E, 0, 0, 0);
                 E = __builtin_amdgcn_mfma_f32_32x32x16_bf16(we, to_bf16(b[0][2 * q], b[0][2 * q + 1]), E, 0, 0, 0);
             } else {
@@ -339,7 +336,10 @@ __device__ __forceinline__ bool tile(const LaunchArgs& a, int tm, int tn, SmemFP
             __builtin_amdgcn_sched_barrier(0);
         }
     };
-    auto due = [&](int t) { return FT > 0 && (((t + 1) % a.check_interval == 0) || (t == nk - 1)); };
+    // the next step with a check (a counter: the remainder of t by a run-time
+    // interval is some forty instructions)
+    int next_check = a.check_interval >= nk ? nk - 1 : a.check_interval - 1;
+    auto due = [&](int t) { return FT > 0 && t == next_check; };
     // the squares over the k prefix of step t, before the step stages the next panel
     auto put_norms = [&]() {
         const int t = opaque_tid();
@@ -373,6 +373,7 @@ __device__ __forceinline__ bool tile(const LaunchArgs& a, int tm, int tn, SmemFP
                 float ref = r0;
                 check<G, FT, INJ>(acc, sm.ck, a, th, t, min((t + 1) * KC, a.K), ref, n, ref, n, fnext, flogged);
                 rebase += ref - r0;
+                next_check = nk - 1 - next_check > a.check_interval ? next_check + a.check_interval : nk - 1;
                 return true;
             }
         }

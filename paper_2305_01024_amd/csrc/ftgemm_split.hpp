@@ -160,42 +160,33 @@ __device__ __forceinline__ bool tile(const LaunchArgs& a, int tm, int tn, SmemSp
 
     // ---- global -> registers: four 16-byte loads, x[e] = rows 4 lq .. + 3 of
     // k = 4 kq + e of A, or k 4 kq .. + 3 of column lq + LQ e of B.
-    // The loads have no alignment beyond a float's and no branch: what lies
-    // outside the matrix is past the resource's end or given an offset there,
-    // and reads as zero.  A load that would straddle the last row of the tile
+    // The loads have no alignment beyond a float's; what lies outside the matrix
+    // is given an offset past the resource's end and reads as zero.  (The loads
+    // stay out of branches: with them in one, the waits for them were coarser.)  A load that would straddle the last row of the tile
     // or the last k is moved back inside, and fix() shifts what it got.
     constexpr int kOutside = (int)0x80000000;
     constexpr int inset = LT;     // the base lies four floats early, so that a moved load's offset is not negative
     auto moved = [&](int off, int rem) { return rem >= LT ? off : rem > 0 ? off - 4 * (LT - rem) : kOutside; };
     const int voff = row_role ? moved((4 * kq * (int)a.lda + LT * lq + inset) * 4, mI - LT * lq) : (lq * (int)a.ldb + 4 * kq + inset) * 4;
-    const int64_t pstride = row_role ? KC * a.lda * 4 : KC * 4;
-    const int64_t estride = (row_role ? a.lda : (int64_t)LQ * a.ldb) * 4;
+    const int pstride = row_role ? KC * (int)a.lda * 4 : KC * 4;
+    const int estride = (row_role ? (int)a.lda : LQ * (int)a.ldb) * 4;
     const bool whole_n = th.nJ == BN;
     const char* const base0 = row_role ? reinterpret_cast<const char*>(a.A + th.i0 - inset)
                                        : reinterpret_cast<const char*>(a.B + (int64_t)th.j0 * a.ldb - inset);
-    const int64_t bytes0 = row_role ? ((int64_t)(a.K - 1) * a.lda + (a.M - th.i0 + inset)) * 4
-                                    : ((int64_t)(a.N - 1 - th.j0) * a.ldb + a.K + inset) * 4;
     constexpr int kRsrcWord3 = 0x00020000;   // raw 32-bit data format
     auto load = [&](f32x4 (&x)[4], int p) {
         const int k0 = p * KC;
-        int vo = voff;
-        if (!row_role && k0 + KC > a.K) vo = moved(voff, a.K - (k0 + 4 * kq));
-        // the end of the resource matters only past the last whole panel and
-        // in B's last column tile
-        int nr[4] = {0x7fffffff, 0x7fffffff, 0x7fffffff, 0x7fffffff};
-        if (!(k0 + KC <= a.K && (row_role || whole_n))) {
+        // the panel's origin in the resource, a load's line or k in a scalar
+        // offset: no address arithmetic in the vector unit and little in the scalar one
+        const auto rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(base0 + (int64_t)p * pstride), (short)0, 0x7fffffff, kRsrcWord3);
+        int vo[4] = {voff, voff, voff, voff};
+        if (!(k0 + KC <= a.K && (row_role || whole_n))) {   // past the last whole panel, or B's last column tile
+            const int vk = row_role ? voff : moved(voff, a.K - (k0 + 4 * kq));
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const int64_t left = k0 < a.K ? bytes0 - p * pstride - e * estride : 0;
-                nr[e] = (int)(left < 0 ? 0 : left > 0x7fffffff ? 0x7fffffff : left);
-            }
+            for (int e = 0; e < 4; ++e) vo[e] = (row_role ? k0 + 4 * kq + e < a.K : lq + LQ * e < th.nJ) ? vk : kOutside;
         }
-        const char* const at = base0 + p * pstride;
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const auto rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(at + e * estride), (short)0, nr[e], kRsrcWord3);
-            x[e] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rs, vo, 0, 0));
-        }
+        for (int e = 0; e < 4; ++e) x[e] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rs, vo[e], e * estride, 0));
     };
     const int shift = (LT - (row_role ? mI : a.K) % LT) % LT;
     auto fix = [&](f32x4 (&x)[4], int k0) {
@@ -358,12 +349,14 @@ __device__ __forceinline__ bool tile(const LaunchArgs& a, int tm, int tn, SmemSp
     };
 
     // injection hook and online check after k-step t; true: the tile leaves the split path
+    int next_check = a.check_interval >= nk ? nk - 1 : a.check_interval - 1;   // (a counter: a remainder by a run-time interval is some forty instructions)
     bool checked = false;
     auto post = [&](int t) -> bool {
         if constexpr (INJ) inject<G>(acc, sm.ck, a, th, t, fnext);
         checked = false;
         if constexpr (FT > 0) {
-            if (((t + 1) % a.check_interval == 0) || (t == nk - 1)) {
+            if (t == next_check) {
+                next_check = nk - 1 - next_check > a.check_interval ? next_check + a.check_interval : nk - 1;
                 float rr[LT], nn[LT];
 #pragma unroll
                 for (int r = 0; r < LT; ++r) { rr[r] = R[r]; nn[r] = n2[r]; }
