@@ -207,14 +207,12 @@ __device__ void tile64(const F64Args& a, int tm, int tn, F64Lds& s) {
     // and 4 pairs of B (k = 2 (tid % 8), +1 of column j = tid / 8 + 32 r) ----
     double ra[4][2], rb[4][2];
     // Interior panels (the whole k-step inside K, the whole tile inside M or
-    // N, 16-byte aligned pairs): one 16-byte buffer load per pair, with the
+    // N): one 16-byte buffer load per pair, at any 8-byte alignment, with the
     // per-lane byte offset fixed for the whole k-loop, the per-step origin in
     // the scalar resource base and the per-slot offset in a scalar register,
     // so the loop carries no vector address arithmetic or bounds selects.
-    const bool vecA = ((reinterpret_cast<uintptr_t>(a.A) & 15) == 0) && ((a.lda & 1) == 0) &&
-                      (int64_t)BK * a.lda * 8 < (int64_t(1) << 31);
-    const bool vecB = ((reinterpret_cast<uintptr_t>(a.B) & 15) == 0) && ((a.ldb & 1) == 0) &&
-                      (int64_t)BN * a.ldb * 8 < (int64_t(1) << 31);
+    const bool vecA = (int64_t)BK * a.lda * 8 < (int64_t(1) << 31);
+    const bool vecB = (int64_t)BN * a.ldb * 8 < (int64_t(1) << 31);
     constexpr int kRsrcWord3 = 0x00020000;   // raw 32-bit data format
     auto load = [&](int t) {
         const Lanes L = lanes();
