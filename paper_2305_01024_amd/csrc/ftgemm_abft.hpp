@@ -915,9 +915,47 @@ __device__ __forceinline__ void finish_tile(const Acc<G>& acc, const CheckLds<G>
     }
     epilogue<G>(acc, a, th, scale);
 }
+// Whole-column tiles store (and load, where beta is not 0) through a buffer
+// resource: a lane's offset is the same for all of its elements, the column goes
+// into the scalar offset, rows past the tile are given an offset past the
+// resource's end.  The 16 loads of a block are issued together: one load, its
+// wait and a store after another (the compiler cannot know that they do not
+// alias) took a memory latency per element and an address computation under a
+// branch.  Before -> after, online, beta = 1: FP32 2048^3 151 -> 138 us,
+// 16384 x 16384 x 64 385 -> 341 us, BF16 2048^3 72.9 -> 68.4 us.  The line:
+// ragged last columns would need a test per store, and offsets are 32 bits.
 template <class G>
 __device__ __forceinline__ void epilogue(const Acc<G>& acc, const LaunchArgs& a, const Thread& th, float scale) {
     const float alpha = a.alpha * scale;
+    if (th.nJ == G::BN && (int64_t)(G::BN + 1) * a.ldc * 4 < (int64_t(1) << 31)) {
+        constexpr int kRsrcWord3 = 0x00020000;   // raw 32-bit data format
+        const int ldc = (int)a.ldc;
+        const auto rs = __builtin_amdgcn_make_buffer_rsrc(a.C + (int64_t)th.j0 * a.ldc + th.i0, (short)0, 0x7fffffff, kRsrcWord3);
+#pragma unroll
+        for (int bi = 0; bi < G::MI; ++bi) {
+            const int i = th.wm * G::TM + 32 * G::row_block(bi, th.wn) + th.l32;
+            const int vo = i < th.mI ? (4 * th.hh * ldc + i) * 4 : (int)0x80000000;
+#pragma unroll
+            for (int bj = 0; bj < G::NI; ++bj) {
+                const int so = (th.wn * G::TN + 32 * G::col_block(bj, th.wm)) * ldc * 4;
+                float v[16];
+                if (a.beta != 0.0f) {
+#pragma unroll
+                    for (int r = 0; r < 16; ++r)
+                        v[r] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rs, vo, so + (8 * (r >> 2) + (r & 3)) * ldc * 4, 0));
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) v[r] = fmaf(a.beta, v[r], alpha * acc[bi][bj][r]);
+                } else {
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) v[r] = alpha * acc[bi][bj][r];
+                }
+#pragma unroll
+                for (int r = 0; r < 16; ++r)
+                    __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, v[r]), rs, vo, so + (8 * (r >> 2) + (r & 3)) * ldc * 4, 0);
+            }
+        }
+        return;
+    }
 #pragma unroll
     for (int bi = 0; bi < G::MI; ++bi) {
         const int i = th.wm * G::TM + 32 * G::row_block(bi, th.wn) + th.l32;

@@ -574,23 +574,33 @@ __device__ void tile64(const F64Args& a, int tm, int tn, F64Lds& s) {
 
     if (FT > 0 && tid == 0) atomicAdd(&a.counters[CNT_CHECKS], s.nchecks);   // written before the last barrier
 
-    // epilogue: C = alpha P + beta C (beta == 0: C is not read)
+    // epilogue: C = alpha P + beta C (beta == 0: C is not read).  The 16 loads of
+    // a block column are issued together (see the FP32 epilogue): online
+    // 2.628 -> 2.592 ms at 4096^3 with beta = 1.
 #pragma unroll
-    for (int bj = 0; bj < 4; ++bj)
+    for (int bj = 0; bj < 4; ++bj) {
+        double c[4][4];
+        if (a.beta != 0.0) {
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const int j = 64 * wn + 16 * bj + 4 * q + lg;
+            for (int q = 0; q < 4; ++q)
+#pragma unroll
+                for (int bi = 0; bi < 4; ++bi) {
+                    const int j = 64 * wn + 16 * bj + 4 * q + lg, i = 64 * wm + 16 * bi + li;
+                    const bool in = i < mI && j < nJ;
+                    const double x = *(in ? a.C + (size_t)(j0 + j) * a.ldc + (i0 + i) : a.C);
+                    c[q][bi] = x;
+                }
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
 #pragma unroll
             for (int bi = 0; bi < 4; ++bi) {
-                const int i = 64 * wm + 16 * bi + li;
-                if (i < mI && j < nJ) {
-                    double* pc = a.C + (size_t)(j0 + j) * a.ldc + (i0 + i);
-                    double v = a.alpha * accm[bj][bi][q];
-                    if (a.beta != 0.0) v = fma(a.beta, *pc, v);
-                    *pc = v;
-                }
+                const int j = 64 * wn + 16 * bj + 4 * q + lg, i = 64 * wm + 16 * bi + li;
+                double v = a.alpha * accm[bj][bi][q];
+                if (a.beta != 0.0) v = fma(a.beta, c[q][bi], v);
+                if (i < mI && j < nJ) a.C[(size_t)(j0 + j) * a.ldc + (i0 + i)] = v;
             }
-        }
+    }
 }
 
 template <int FT, bool INJ>
