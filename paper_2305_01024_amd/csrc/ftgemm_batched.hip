@@ -6,7 +6,7 @@
 // stays balanced: for 1024 problems of 32 to 2048 the dearest workgroup has
 // 0.7% more than the mean (7% with every round forwards).  Sizes that divide by
 // nothing took element loads in the earlier tiles: 5.54 ms for that batch
-// (half FP32, half BF16), 2.00 ms with the split and bf16m tiles.  Each
+// (half FP32, half BF16), 1.80 ms with the split and bf16m tiles.  Each
 // item runs the same tile computation as the single-problem kernels (the
 // threadblock-level online ABFT of section 4.2.3, with its own encode,
 // checksum update, checks and correction), on the item's problem: one tile

@@ -22,15 +22,15 @@
 // a check: the owners' reads of whole rows and columns from LDS are gone.
 //
 // What bounds it: at 256 x 256 and 8192^3 the matrix instructions take 3.1 ms
-// of 5.3 at the 1.9-2.0 GHz the chip then runs at (six times the library's
+// of 5.2 at the 1.9-2.0 GHz the chip then runs at (six times the library's
 // bf16 product of that size takes 5.8 ms).  Vector instructions issue beside
 // matrix instructions of either wavefront on the SIMD (measured: six between
 // two MFMAs are 90-95% hidden; v_dot2 is the exception, it waits for the matrix
 // pipe), so the split, the encodings and the reference updates of a panel,
 // about 190 instructions per wavefront, are dealt out between its 48 MFMAs.
-// 8192^3 online: 8.71 ms on the FP32 instructions, 5.32 ms here; 2048^3 (one
+// 8192^3 online: 8.72 ms on the FP32 instructions, 5.19 ms here; 2048^3 (one
 // 128 x 128 tile per compute unit, bound by the latency of a panel: LDS reads
-// after the barrier, split and store before the next) 0.210 -> 0.150 ms.
+// after the barrier, split and store before the next) 0.210 -> 0.138 ms.
 //
 // Where the split does not hold: bits below bf16's smallest denormal (operand
 // elements under 2^-110), and Inf, NaN or norms near overflow.  Both are seen
