@@ -126,6 +126,40 @@ def test_not_splittable(h, cfg, value):
         F.ftgemm_set_config(h, None)
 
 
+@pytest.mark.parametrize("cfg", CONFIGS)
+@pytest.mark.parametrize("value", [0.0, 1e-38])
+def test_faults_beside_tiles_without(h, cfg, value):
+    """Faults in the first and the last tile, each applied and corrected once,
+    with every tile on the split (0) or some elements too small for it."""
+    m = n = 300
+    k = 512
+    r = np.random.default_rng(21)
+    A, B = r.standard_normal((m, k)).astype(np.float32), r.standard_normal((k, n)).astype(np.float32)
+    if value:
+        A[280, 20] = value      # the last row of tiles
+        B[30, 5] = value        # the first column of tiles
+    last = (m - 1) // cfg[0]
+    sites = np.zeros(2, F.FAULT_DTYPE)
+    sites["tile_m"] = sites["tile_n"] = (0, last)
+    sites["kstep"], sites["row"], sites["col"] = (1, 9), (17, 30), (40, 20)
+    sites["kind"], sites["payload"] = F.FAULT_ADD, 1e6
+    F.ftgemm_set_config(h, cfg)
+    F.ftgemm_set_injection(h, sites)
+    try:
+        st, C, rep = _run(h, A, B, 2)
+        log = F.ftgemm_get_injection_log(h)
+    finally:
+        F.ftgemm_set_injection(h, None)
+        F.ftgemm_set_config(h, None)
+    assert st == F.OK and len(log) == 2 and rep.report.corrected == 2 and rep.report.n_events == 2
+    A64, B64 = A.astype(np.float64), B.astype(np.float64)
+    bound = (k + 2) * 2.0 ** -24 * (np.abs(A64) @ np.abs(B64))
+    for t, row, col in ((0, 17, 40), (last, 30, 20)):
+        i = t * cfg[0] + row
+        bound[i, t * cfg[0] + col] += bound[i].sum()     # rebuilt from the row's checksum
+    assert np.max(np.abs(C - A64 @ B64) / bound) <= 1.0
+
+
 def test_tiles_of_a_batch(h):
     """The batch's FP32 tiles over ragged sizes against the products."""
     import torch
