@@ -96,26 +96,32 @@ __device__ __forceinline__ float bf_hi(unsigned x) { return __uint_as_float(x & 
 // Norm squares from here on may overflow an intermediate sum of the parts.
 constexpr float kHugeNorm2 = 3.3e38f;
 
-// Whether every operand element of the tile can take the split path: asked
-// before a tile with faults to inject, which must not be computed twice (the
-// faults are logged as they are applied).  Tiles without one leave the split
+// Whether the tile's operands can take the split path: asked before a tile with
+// faults to inject, which must not be computed twice (the faults are logged as
+// they are applied).  No element is too small, and what a thread reads of all
+// lines has a sum of squares that keeps every line's norm, over all of K, below
+// the one at which a check leaves.  Tiles without a fault leave the split
 // as they do without injection; with the scan in every tile, and a division
 // per element, a launch of 8192^3 with one fault took 21.2 ms.
 template <class G>
 __device__ __forceinline__ bool splittable(const LaunchArgs& a, const Thread& th, int* flag) {
-    auto bad = [](float x) {
+    bool small = false;
+    float sq = 0.f;
+    auto see = [&](float x) {
         const unsigned u = __float_as_uint(x) & 0x7fffffffu;
-        return (u != 0 && u < 0x0d800000u) || u > 0x5f000000u;   // below 2^-100, above 2^63
+        small |= u != 0 && u < 0x0d800000u;   // below 2^-100
+        sq = fmaf(x, x, sq);
     };
-    bool b = false;
     const int i = th.tid % G::BM;
     if (i < th.mI)
-        for (int k = th.tid / G::BM; k < a.K; k += G::NT / G::BM) b |= bad(a.A[(int64_t)k * a.lda + th.i0 + i]);
+        for (int k = th.tid / G::BM; k < a.K; k += G::NT / G::BM) see(a.A[(int64_t)k * a.lda + th.i0 + i]);
     for (int j = th.tid / 64; j < th.nJ; j += G::NT / 64)
-        for (int k = th.tid % 64; k < a.K; k += 64) b |= bad(a.B[(int64_t)(th.j0 + j) * a.ldb + k]);
+        for (int k = th.tid % 64; k < a.K; k += 64) see(a.B[(int64_t)(th.j0 + j) * a.ldb + k]);
+    // (a factor of two for the sums' own rounding)
+    const bool bad = small || !(sq < kHugeNorm2 / (2 * G::NT));
     if (th.tid == 0) *flag = 0;
     __syncthreads();
-    if (b) *flag = 1;
+    if (bad) *flag = 1;
     __syncthreads();
     const bool ok = __builtin_amdgcn_readfirstlane(*flag) == 0;
     __syncthreads();
