@@ -96,29 +96,66 @@ __device__ __forceinline__ float bf_hi(unsigned x) { return __uint_as_float(x & 
 // Norm squares from here on may overflow an intermediate sum of the parts.
 constexpr float kHugeNorm2 = 3.3e38f;
 
+constexpr int kRsrcWord3 = 0x00020000;        // raw 32-bit data format
+constexpr int kOutside = (int)0x80000000;     // offset past a resource's end: reads as zero
+constexpr int kLines = 4;                     // floats of a load
+// Offset of a load with `rem` floats of its line left: one that would straddle
+// the end is moved back inside.
+__device__ __forceinline__ int moved(int off, int rem) { return rem >= kLines ? off : rem > 0 ? off - 4 * (kLines - rem) : kOutside; }
+
 // Whether the tile's operands can take the split path: asked before a tile with
 // faults to inject, which must not be computed twice (the faults are logged as
 // they are applied).  No element is too small, and what a thread reads of all
 // lines has a sum of squares that keeps every line's norm, over all of K, below
-// the one at which a check leaves.  Tiles without a fault leave the split
-// as they do without injection; with the scan in every tile, and a division
-// per element, a launch of 8192^3 with one fault took 21.2 ms.
+// the one at which a check leaves.  (Quads at the last rows may look at the tile
+// above too.)  Tiles without a fault leave the split as they do without
+// injection.  16-byte loads, 32 in flight per thread: one fault adds 0.30 ms to a
+// launch of 8192^3, 0.03 to 4096^3 and 0.016 to 2048^3 (one 4-byte load after
+// another: 1.29, 0.97 and 0.41 ms).
 template <class G>
 __device__ __forceinline__ bool splittable(const LaunchArgs& a, const Thread& th, int* flag) {
-    bool small = false;
-    float sq = 0.f;
-    auto see = [&](float x) {
-        const unsigned u = __float_as_uint(x) & 0x7fffffffu;
-        small |= u != 0 && u < 0x0d800000u;   // below 2^-100
-        sq = fmaf(x, x, sq);
+    constexpr int RQ = G::BM / kLines, PK = G::NT / RQ;     // row quads; k per pass over A
+    constexpr int CK = 64, NQ = CK / kLines, CC = G::NT / NQ;   // k and k-quads of a chunk; columns per pass over B
+    constexpr int PA = CK / PK, PB = G::BN / CC, L = PA + PB;
+    const int rq = th.tid % RQ, ka = th.tid / RQ, kq = th.tid % NQ, cb = th.tid / NQ;
+    const float* const baseA = a.A + th.i0 - kLines;
+    const float* const baseB = a.B + (int64_t)th.j0 * a.ldb - kLines;
+    const int vA = moved((ka * (int)a.lda + kLines * rq + kLines) * 4, th.mI - kLines * rq);
+    const int vB = (cb * (int)a.ldb + kLines * kq + kLines) * 4;
+    auto load = [&](f32x4 (&x)[L], int left) {   // the chunk with `left` k to go
+        const int64_t k0 = (int64_t)a.K - left;
+#pragma unroll
+        for (int e = 0; e < PA; ++e) {
+            const auto rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(baseA + (k0 + e * PK) * a.lda), (short)0, 0x7fffffff, kRsrcWord3);
+            x[e] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rs, e * PK + ka < left ? vA : kOutside, 0, 0));
+        }
+        const auto rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(baseB + k0), (short)0, 0x7fffffff, kRsrcWord3);
+        const int vk = moved(vB, left - kLines * kq);
+#pragma unroll
+        for (int e = 0; e < PB; ++e)
+            x[PA + e] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rs, cb + CC * e < th.nJ ? vk : kOutside, e * CC * (int)a.ldb * 4, 0));
     };
-    const int i = th.tid % G::BM;
-    if (i < th.mI)
-        for (int k = th.tid / G::BM; k < a.K; k += G::NT / G::BM) see(a.A[(int64_t)k * a.lda + th.i0 + i]);
-    for (int j = th.tid / 64; j < th.nJ; j += G::NT / 64)
-        for (int k = th.tid % 64; k < a.K; k += 64) see(a.B[(int64_t)(th.j0 + j) * a.ldb + k]);
-    // (a factor of two for the sums' own rounding)
-    const bool bad = small || !(sq < kHugeNorm2 / (2 * G::NT));
+    unsigned least = 0xffffffffu;   // smallest of 2 |x| - 1 as integers, where 0 is the largest
+    float sq = 0.f;
+    auto see = [&](const f32x4 (&x)[L]) {
+#pragma unroll
+        for (int e = 0; e < L; ++e)
+#pragma unroll
+            for (int q = 0; q < kLines; ++q) {
+                least = min(least, (__float_as_uint(x[e][q]) << 1) - 1u);
+                sq = fmaf(x[e][q], x[e][q], sq);
+            }
+    };
+    f32x4 x0[L], x1[L];
+    load(x0, a.K);
+    for (int left = a.K; left > 0; left -= 2 * CK) {
+        load(x1, left - CK);
+        see(x0);
+        load(x0, left - 2 * CK);
+        see(x1);
+    }
+    // 2^-100; a factor of two for the sums' own rounding
+    const bool bad = least < 2 * 0x0d800000u - 1 || !(sq < kHugeNorm2 / (2 * G::NT));
     if (th.tid == 0) *flag = 0;
     __syncthreads();
     if (bad) *flag = 1;
@@ -136,7 +173,7 @@ __device__ __forceinline__ bool tile(const LaunchArgs& a, int tm, int tn, SmemSp
     constexpr int NT = G::NT, TM = G::TM, TN = G::TN, MI = G::MI, NI = G::NI;
     constexpr int BK = 32;              // k-step of the interface: two panels
     constexpr int NE = WM * WN / 2;     // wavefronts per role
-    constexpr int LT = 4;               // lines per thread
+    constexpr int LT = kLines;          // lines per thread
     constexpr int LQ = BM / LT;         // line groups per panel
     static_assert(BM == BN && NT == 2 * BM && LQ % 32 == 0 && NI == 2, "four lines x 4 k per thread");
 
@@ -179,16 +216,13 @@ __device__ __forceinline__ bool tile(const LaunchArgs& a, int tm, int tn, SmemSp
     // is given an offset past the resource's end and reads as zero.  (The loads
     // stay out of branches: with them in one, the waits for them were coarser.)  A load that would straddle the last row of the tile
     // or the last k is moved back inside, and fix() shifts what it got.
-    constexpr int kOutside = (int)0x80000000;
     constexpr int inset = LT;     // the base lies four floats early, so that a moved load's offset is not negative
-    auto moved = [&](int off, int rem) { return rem >= LT ? off : rem > 0 ? off - 4 * (LT - rem) : kOutside; };
     const int voff = row_role ? moved((4 * kq * (int)a.lda + LT * lq + inset) * 4, mI - LT * lq) : (lq * (int)a.ldb + 4 * kq + inset) * 4;
     const int pstride = row_role ? KC * (int)a.lda * 4 : KC * 4;
     const int estride = (row_role ? (int)a.lda : LQ * (int)a.ldb) * 4;
     const bool whole_n = th.nJ == BN;
     const char* const base0 = row_role ? reinterpret_cast<const char*>(a.A + th.i0 - inset)
                                        : reinterpret_cast<const char*>(a.B + (int64_t)th.j0 * a.ldb - inset);
-    constexpr int kRsrcWord3 = 0x00020000;   // raw 32-bit data format
     auto load = [&](f32x4 (&x)[4], int p) {
         const int k0 = p * KC;
         // the panel's origin in the resource, a load's line or k in a scalar
