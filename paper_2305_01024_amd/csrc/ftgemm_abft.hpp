@@ -203,7 +203,7 @@ struct CheckLds {
                             // launch's counter once, at the end of the tile, so that the loop
                             // carries no global atomic whose completion a later wait would see
     int nflagged;           // wavefronts that flagged a line at the current check (0 between checks)
-    int bail;               // the tile's operands do not fit the kernel's number format (split FP32 only)
+    int bail;               // the tile's operands do not fit the kernel's number range (split FP32 only)
 };
 
 // Clears the tile's check state; before the tile's first barrier.  Census
@@ -424,13 +424,15 @@ __device__ __forceinline__ Thread opaque_lanes(const Thread& th) {
 // LATE: called after that first barrier, for what the caller left to other
 // threads in LDS before the check (its references); returns true to leave
 // without a check, on a value that is the same for the whole workgroup.
+// unit: what 1 in the accumulators and references stands for (events log values
+// in the product's own units).
 struct NoLate {
     __device__ __forceinline__ bool operator()() const { return false; }
 };
 template <class G, int FT, bool INJ, class LATE = NoLate>
 __device__ __forceinline__ bool check(Acc<G>& acc, CheckLds<G>& s, const LaunchArgs& a, const Thread& th_loop, int t, int kp,
                                       float& Rr, float& na2, float& Sc, float& nb2, int fnext, int& flogged,
-                                      LATE&& late = LATE{}) {
+                                      LATE&& late = LATE{}, float unit = 1.0f) {
     constexpr int MI = G::MI, NI = G::NI, TM = G::TM, TN = G::TN, WM = G::WM, WN = G::WN, NW = G::NW;
     const Thread th = opaque_lanes(th_loop);
     const int lane = th.lane, l32 = th.l32, hh = th.hh, wm = th.wm, wn = th.wn;
@@ -600,8 +602,8 @@ __device__ __forceinline__ bool check(Acc<G>& acc, CheckLds<G>& s, const LaunchA
                 ftgemm_event_t E;
                 E.problem = a.problem; E.tile_m = th.tm; E.tile_n = th.tn; E.kstep = t;
                 E.row = fr; E.col = fc; E.kind = FTGEMM_EV_CORRECTED; E.n_rows = 1; E.n_cols = 1;
-                E.pad_ = 0; E.value_before = oldv; E.value_after = newv;
-                E.r_row = s.bc[1]; E.r_col = s.bc[3]; E.tau_row = s.bc[2]; E.tau_col = s.bc[4];
+                E.pad_ = 0; E.value_before = oldv * unit; E.value_after = newv * unit;
+                E.r_row = s.bc[1] * unit; E.r_col = s.bc[3] * unit; E.tau_row = s.bc[2] * unit; E.tau_col = s.bc[4] * unit;
                 a.events[e] = E;
             }
         }
@@ -626,8 +628,8 @@ __device__ __forceinline__ bool check(Acc<G>& acc, CheckLds<G>& s, const LaunchA
                 E.problem = a.problem; E.tile_m = th.tm; E.tile_n = th.tn; E.kstep = t;
                 E.row = fr; E.col = fc; E.kind = kind; E.n_rows = nr; E.n_cols = ncl; E.pad_ = 0;
                 E.value_before = E.value_after = 0.f;
-                E.r_row = fr >= 0 ? s.bc[1] : 0.f; E.tau_row = fr >= 0 ? s.bc[2] : 0.f;
-                E.r_col = fc >= 0 ? s.bc[3] : 0.f; E.tau_col = fc >= 0 ? s.bc[4] : 0.f;
+                E.r_row = fr >= 0 ? s.bc[1] * unit : 0.f; E.tau_row = fr >= 0 ? s.bc[2] * unit : 0.f;
+                E.r_col = fc >= 0 ? s.bc[3] * unit : 0.f; E.tau_col = fc >= 0 ? s.bc[4] * unit : 0.f;
                 a.events[e] = E;
             }
         }

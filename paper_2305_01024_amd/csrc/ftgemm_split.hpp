@@ -32,10 +32,13 @@
 // 128 x 128 tile per compute unit, bound by the latency of a panel: LDS reads
 // after the barrier, split and store before the next) 0.210 -> 0.138 ms.
 //
-// Where the split does not hold: bits below bf16's smallest denormal (operand
-// elements under 2^-110), and Inf, NaN or norms near overflow.  Both are seen
-// before the first check that would cover them; the tile is then computed
-// again by f32::tile, which is what the kernel's callers do on `false`.
+// Every operand is multiplied by 2^16 as it is split, and the sums by 2^-32 at the
+// end (both exact): a binary32 number, denormals included, is then a multiple of
+// bf16's smallest denormal 2^-133, so none is too small for its three parts.
+// Where the split does not hold: Inf, NaN and lines whose norm is 2^43 or more,
+// whose scaled sums could overflow.  Those are seen before the first check that
+// would cover them; the tile is then computed again by f32::tile, which is what
+// the kernel's callers do on `false`.
 #pragma once
 
 #include "ftgemm_fp32.hpp"
@@ -92,9 +95,15 @@ __device__ __forceinline__ unsigned pack_bf16(float a, float b) {
 }
 __device__ __forceinline__ float bf_lo(unsigned x) { return __uint_as_float(x << 16); }
 __device__ __forceinline__ float bf_hi(unsigned x) { return __uint_as_float(x & 0xffff0000u); }
+__device__ __forceinline__ float uniform(float x) {   // a wave-uniform value, in a scalar register
+    return __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, x)));
+}
 
-// Norm squares from here on may overflow an intermediate sum of the parts.
-constexpr float kHugeNorm2 = 3.3e38f;
+constexpr float kScale = 65536.0f;                        // of an operand
+constexpr float kUnit = 1.0f / (kScale * kScale);         // one unit of a scaled product
+// Squares of scaled norms from here on leave the split: below, a product is less
+// than 2^118 in size and a line's sum over 256 of them less than 2^126.
+constexpr float kHugeNorm2 = 0x1p118f;
 
 constexpr int kRsrcWord3 = 0x00020000;        // raw 32-bit data format
 constexpr int kOutside = (int)0x80000000;     // offset past a resource's end: reads as zero
@@ -103,11 +112,13 @@ constexpr int kLines = 4;                     // floats of a load
 // the end is moved back inside.
 __device__ __forceinline__ int moved(int off, int rem) { return rem >= kLines ? off : rem > 0 ? off - 4 * (kLines - rem) : kOutside; }
 
-// Whether the tile's operands can take the split path: asked before a tile with
-// faults to inject, which must not be computed twice (the faults are logged as
-// they are applied).  No element is too small, and what a thread reads of all
-// lines has a sum of squares that keeps every line's norm, over all of K, below
-// the one at which a check leaves.  (Quads at the last rows may look at the tile
+// Whether the tile's operands can take the split path as they are: asked before a
+// tile with faults to inject, which must not be computed twice (the faults are
+// logged as they are applied) and whose accumulators are not scaled (a bit flip
+// is one of the accumulator as FP32 arithmetic has it).  No element is too
+// small for its parts, and what a thread reads of all lines has a sum of squares
+// that keeps every line's norm, over all of K, below the one at which a check
+// leaves.  (Quads at the last rows may look at the tile
 // above too.)  Tiles without a fault leave the split as they do without
 // injection.  16-byte loads, 32 in flight per thread: one fault adds 0.30 ms to a
 // launch of 8192^3, 0.03 to 4096^3 and 0.016 to 2048^3 (one 4-byte load after
@@ -205,7 +216,7 @@ __device__ __forceinline__ bool tile(const LaunchArgs& a, int tm, int tn, SmemSp
     if constexpr (INJ) {
         gather_faults<G>(sm.ck, a, th);
         __syncthreads();
-        faulty = __builtin_amdgcn_readfirstlane(sm.ck.nf) > 0;
+        faulty = __builtin_amdgcn_readfirstlane(sm.ck.nf) > 0;   // (kept unscaled, see splittable)
         if (faulty && !splittable<G>(a, th, &sm.ck.bail)) return false;
     }
     __syncthreads();
@@ -256,18 +267,28 @@ __device__ __forceinline__ bool tile(const LaunchArgs& a, int tm, int tn, SmemSp
         }
     };
 
-    // ---- registers -> LDS: y[r][q] = k 4 kq + q of line r
+    // ---- registers -> LDS: y[r][q] = k 4 kq + q of line r, scaled
+    const float scale = INJ ? uniform(faulty ? 1.0f : kScale) : kScale, unit = INJ ? uniform(faulty ? 1.0f : kUnit) : kUnit;
     float y[LT][4];
-    // Low halves of the third parts before they are rounded to bf16.  A
-    // normal one has at most 8 significant bits, so its low half is 0; where
-    // x is so small (below 2^-110) that its last bits are under bf16's
-    // smallest denormal, they show here.
-    unsigned lost = 0;
+    // (One scalar per arm, and an asm behind it: the multiplies would otherwise be
+    // taken out of the arms, leaving a copy of every register in their place.)
     auto transpose = [&](const f32x4 (&x)[4]) {
+        float sc = scale;
+        if (row_role) {
+            asm volatile("; rows" : "+s"(sc));
 #pragma unroll
-        for (int r = 0; r < LT; ++r)
+            for (int r = 0; r < LT; ++r)
 #pragma unroll
-            for (int q = 0; q < 4; ++q) y[r][q] = row_role ? x[q][r] : x[r][q];
+                for (int q = 0; q < 4; ++q) y[r][q] = x[q][r] * sc;
+            asm volatile("; of A" : "+v"(y[0][0]));
+        } else {
+            asm volatile("; columns" : "+s"(sc));
+#pragma unroll
+            for (int r = 0; r < LT; ++r)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) y[r][q] = x[r][q] * sc;
+            asm volatile("; of B" : "+v"(y[0][0]));
+        }
     };
     constexpr int PS = BM / 32 * 64 * 8;   // halves per part
     constexpr int BUF = PARTS * PS;        // halves per panel
@@ -283,10 +304,7 @@ __device__ __forceinline__ bool tile(const LaunchArgs& a, int tm, int tn, SmemSp
         part[0][h] = pack_bf16(x0, x1);
         const float e0 = x0 - bf_lo(part[0][h]), e1 = x1 - bf_hi(part[0][h]);
         part[1][h] = pack_bf16(e0, e1);
-        const float l0 = e0 - bf_lo(part[1][h]), l1 = e1 - bf_hi(part[1][h]);
-        part[2][h] = pack_bf16(l0, l1);
-        lost |= __float_as_uint(l0) | __float_as_uint(l1);
-        asm volatile("" : "+v"(lost));
+        part[2][h] = pack_bf16(e0 - bf_lo(part[1][h]), e1 - bf_hi(part[1][h]));
     };
     auto store_line = [&](int buf, int r) {
         unsigned short* d = dst0 + buf * BUF + doff[r];
@@ -411,11 +429,11 @@ __device__ __forceinline__ bool tile(const LaunchArgs& a, int tm, int tn, SmemSp
                 for (int r = 0; r < LT; ++r) { rr[r] = R[r]; nn[r] = n2[r]; }
                 ReduceScatter<LT, 1, 0>::run(rr, lane);
                 ReduceScatter<LT, 1, 0>::run(nn, lane);
-                if ((lost & 0xffffu) != 0 || !(nn[0] < kHugeNorm2)) sm.ck.bail = 1;
+                if (!(nn[0] < kHugeNorm2)) sm.ck.bail = 1;
                 const float r0 = rr[0] + rebase;
                 float ref = r0;
                 auto left = [&]() { return __builtin_amdgcn_readfirstlane(sm.ck.bail) != 0; };
-                if (check<G, FT, INJ>(acc, sm.ck, a, th, t, min((t + 1) * BK, a.K), ref, nn[0], ref, nn[0], fnext, flogged, left))
+                if (check<G, FT, INJ>(acc, sm.ck, a, th, t, min((t + 1) * BK, a.K), ref, nn[0], ref, nn[0], fnext, flogged, left, unit))
                     return true;
                 rebase += ref - r0;
                 checked = true;
@@ -456,12 +474,24 @@ __device__ __forceinline__ bool tile(const LaunchArgs& a, int tm, int tn, SmemSp
                 for (int bj = 0; bj < NI; ++bj)
 #pragma unroll
                     for (int r = 0; r < 16; ++r) z = fmaf(acc[bi][bj][r], 0.f, z);
-            if ((lost & 0xffffu) != 0 || !(z == 0.f)) sm.ck.bail = 1;
+            if (!(z == 0.f)) sm.ck.bail = 1;
             __syncthreads();
             if (__builtin_amdgcn_readfirstlane(sm.ck.bail)) return false;
         }
     }
-    finish_tile<G, FT>(acc, sm.ck, a, th, 1.0f);
+    // back to the product's units with alpha, unless alpha is so small that
+    // the factor would be denormal
+    float factor = unit;
+    if (fabsf(a.alpha) < 0x1p-94f) {
+        factor = 1.0f;
+#pragma unroll
+        for (int bi = 0; bi < MI; ++bi)
+#pragma unroll
+            for (int bj = 0; bj < NI; ++bj)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) acc[bi][bj][r] *= unit;
+    }
+    finish_tile<G, FT>(acc, sm.ck, a, th, factor);
     return true;
 }
 

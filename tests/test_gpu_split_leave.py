@@ -1,5 +1,7 @@
 """GPU tests of what FP32 tiles on the three-way bf16 split do with operands
-outside its range: what a discarded pass leaves behind."""
+outside its range: which operands leave it (none for being small: the bits of a
+product scaled by powers of two are those of the unscaled one), and what a
+discarded pass leaves behind."""
 import numpy as np
 import pytest
 
@@ -47,6 +49,14 @@ def _run(h, A, B, level, tol=0.0, cfg=None, sites=None):
 def _operands(m, n, k, seed):
     r = np.random.default_rng(seed)
     return r.standard_normal((m, k)).astype(np.float32), r.standard_normal((k, n)).astype(np.float32)
+
+
+def _ratio(C, A, B):
+    """Largest element error in units of (k + 2) 2^-24 (|A||B|)_ij + k 2^-149 (one
+    rounding per addition, also where the sums are denormal)."""
+    A64, B64 = A.astype(np.float64), B.astype(np.float64)
+    k = A.shape[1]
+    return np.max(np.abs(C - A64 @ B64) / ((k + 2) * 2.0 ** -24 * (np.abs(A64) @ np.abs(B64)) + k * 2.0 ** -149))
 
 
 def _faults(cfg, last):
@@ -103,3 +113,65 @@ def test_faults_among_large_operands_of_a_batch(h, size):
     finally:
         F.ftgemm_set_injection(h, None)
     assert len(log) == 1 and int(log["check_step"][0]) >= 0
+
+
+@pytest.mark.parametrize("cfg", CONFIGS)
+@pytest.mark.parametrize("level", [0, 1, 2])
+@pytest.mark.parametrize("ea, eb", [(-103, 30), (-106, 30), (-109, 30), (-112, 30), (-118, 36), (-125, 30), (30, -112),
+                                    (-20, -90), (36, -30), (-60, -40)])
+def test_scaled_operands_keep_their_bits(h, cfg, level, ea, eb):
+    """Full 24-bit mantissas times powers of two: no element leaves the split
+    for being small, so the product's bits are the unscaled one's.  (The first
+    32 k add exact zeros and give every line an ordinary norm.)"""
+    m, n, k = 200, 140, 150
+    r = np.random.default_rng(34)
+    A = ((1 + r.random((m, k))) * r.choice([-1, 1], (m, k))).astype(np.float32)
+    B = ((1 + r.random((k, n))) * r.choice([-1, 1], (k, n))).astype(np.float32)
+    B[:16], A[:, 16:32] = 0.0, 0.0
+    C = {}
+    for sa, sb in ((0, 0), (ea, eb)):
+        X, Y = A.copy(), B.copy()
+        X[:, 32:] *= np.float32(2.0 ** sa)
+        Y[32:] *= np.float32(2.0 ** sb)
+        st, c, rep, _ = _run(h, X, Y, level, cfg=cfg)
+        assert st == F.OK and rep.report.n_events == 0
+        C[sa] = np.ldexp(c.astype(np.float64), -sa - sb)
+    assert _ratio(C[0], A, B) <= 1.0
+    assert np.array_equal(C[0], C[ea])
+
+
+@pytest.mark.parametrize("cfg", CONFIGS)
+@pytest.mark.parametrize("level", [0, 1, 2])
+@pytest.mark.parametrize("scale", [2.0 ** -103, 2.0 ** -109, 2.0 ** -118, 2.0 ** -126, 2.0 ** -140])
+def test_small_among_ordinary(h, cfg, level, scale):
+    """Rows of ordinary norm whose products come from their small elements only, down to denormals."""
+    m, n, k = 300, 140, 70
+    A, B = _operands(m, n, k, 35)
+    B[:35, :] = 0.0
+    A[:, 35:] *= np.float32(scale)
+    B[35:, :] *= np.float32(2.0 ** 30)
+    st, C, rep, _ = _run(h, A, B, level, cfg=cfg)
+    assert st == F.OK and rep.report.n_events == 0 and _ratio(C, A, B) <= 1.0
+
+
+@pytest.mark.parametrize("cfg", CONFIGS)
+@pytest.mark.parametrize("level", [0, 2])
+@pytest.mark.parametrize("e", [-62, -66, -70])
+def test_products_below_the_normal_range(h, cfg, level, e):
+    A, B = _operands(256, 130, 64, 36)
+    A, B = A * np.float32(2.0 ** e), B * np.float32(2.0 ** e)
+    st, C, rep, _ = _run(h, A, B, level, cfg=cfg)
+    assert st == F.OK and rep.report.n_events == 0 and _ratio(C, A, B) <= 1.0
+
+
+@pytest.mark.parametrize("cfg", CONFIGS)
+@pytest.mark.parametrize("k", [4, 16, 17, 18, 25, 31, 32, 33])
+def test_short_positive_sums(h, cfg, k):
+    """Sums of one sign over a few k, where the partial products round in one direction the most:
+    the 2-norm error stays below that of a chain of K additions (an error of 2^-24 / sqrt(3) of each of the sums,
+    which grow like i / K: sqrt(K / 9) 2^-24 in all) and a rounding of the result."""
+    r = np.random.default_rng(k)
+    A, B = r.random((256, k)).astype(np.float32), r.random((k, 256)).astype(np.float32)
+    st, C, rep, _ = _run(h, A, B, 2, cfg=cfg)
+    P = A.astype(np.float64) @ B.astype(np.float64)
+    assert st == F.OK and np.linalg.norm(C - P) / np.linalg.norm(P) <= (np.sqrt(k / 9.0) + 1.0) * 2.0 ** -24
