@@ -424,10 +424,13 @@ __device__ __forceinline__ Thread opaque_lanes(const Thread& th) {
 // LATE: called after that first barrier, for what the caller left to other
 // threads in LDS before the check (its references); returns true to leave
 // without a check, on a value that is the same for the whole workgroup.
+// LATE::flagged: called by the whole workgroup when a line was flagged, before
+// anything is logged or corrected; returns true to leave likewise.
 // unit: what 1 in the accumulators and references stands for (events log values
 // in the product's own units).
 struct NoLate {
     __device__ __forceinline__ bool operator()() const { return false; }
+    __device__ __forceinline__ bool flagged() const { return false; }
 };
 template <class G, int FT, bool INJ, class LATE = NoLate>
 __device__ __forceinline__ bool check(Acc<G>& acc, CheckLds<G>& s, const LaunchArgs& a, const Thread& th_loop, int t, int kp,
@@ -517,9 +520,12 @@ __device__ __forceinline__ bool check(Acc<G>& acc, CheckLds<G>& s, const LaunchA
         flogged = fnext;
     }
     __syncthreads();
-    if (__builtin_amdgcn_readfirstlane(s.nflagged) == 0) return false;
+    // (the hint keeps what follows, and its scalar registers, out of the k-loop's
+    // layout: FP8 online 8192^3 1.435 -> 1.327 ms)
+    if (__builtin_expect(__builtin_amdgcn_readfirstlane(s.nflagged) == 0, 1)) return false;
 
     // rare path: something was flagged (uniform branch)
+    if (late.flagged()) return true;
     int nr = 0, ncl = 0, fr = -1, fc = -1;
 #pragma unroll
     for (int w = 0; w < NW; ++w) {

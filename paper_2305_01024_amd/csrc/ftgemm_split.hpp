@@ -112,61 +112,78 @@ constexpr int kLines = 4;                     // floats of a load
 // the end is moved back inside.
 __device__ __forceinline__ int moved(int off, int rem) { return rem >= kLines ? off : rem > 0 ? off - 4 * (kLines - rem) : kOutside; }
 
-// Whether the tile's operands can take the split path as they are: asked before a
-// tile with faults to inject, which must not be computed twice (the faults are
-// logged as they are applied) and whose accumulators are not scaled (a bit flip
-// is one of the accumulator as FP32 arithmetic has it).  No element is too
-// small for its parts, and what a thread reads of all lines has a sum of squares
-// that keeps every line's norm, over all of K, below the one at which a check
-// leaves.  (Quads at the last rows may look at the tile
-// above too.)  Tiles without a fault leave the split as they do without
-// injection.  16-byte loads, 32 in flight per thread: one fault adds 0.30 ms to a
-// launch of 8192^3, 0.03 to 4096^3 and 0.016 to 2048^3 (one 4-byte load after
-// another: 1.29, 0.97 and 0.41 ms).
-template <class G>
-__device__ __forceinline__ bool splittable(const LaunchArgs& a, const Thread& th, int* flag) {
+// Whether the tile's operands can take the split path over all of K, multiplied
+// by `scale`: asked before the tile does what must not be done twice.
+//   * A tile with faults to inject asks first (they are logged as they are
+//     applied).  Its accumulators are not scaled (a bit flip is one of the
+//     accumulator as FP32 arithmetic has it), so no element may be too small for
+//     its parts.  16-byte loads, 32 in flight per thread (DEEP): one fault adds
+//     0.30 ms to a launch of 8192^3, 0.03 to 4096^3 and 0.016 to 2048^3 (one 4-byte
+//     load after another: 1.29, 0.97 and 0.41 ms).
+//   * Any other tile asks at its first flag, if k is left, with the few registers
+//     that are free there.
+// What a thread reads of all lines has a sum of squares that keeps every line's
+// norm below the one at which a check leaves.  (Quads at the last rows may look
+// at the tile above too.)
+template <class G, bool DEEP>
+__device__ __forceinline__ bool splittable(const LaunchArgs& a, const Thread& th, int* flag, float scale) {
     constexpr int RQ = G::BM / kLines, PK = G::NT / RQ;     // row quads; k per pass over A
     constexpr int CK = 64, NQ = CK / kLines, CC = G::NT / NQ;   // k and k-quads of a chunk; columns per pass over B
-    constexpr int PA = CK / PK, PB = G::BN / CC, L = PA + PB;
+    constexpr int P = CK / PK;                              // passes
+    static_assert(P == G::BN / CC, "as many passes over A as over B");
     const int rq = th.tid % RQ, ka = th.tid / RQ, kq = th.tid % NQ, cb = th.tid / NQ;
     const float* const baseA = a.A + th.i0 - kLines;
     const float* const baseB = a.B + (int64_t)th.j0 * a.ldb - kLines;
     const int vA = moved((ka * (int)a.lda + kLines * rq + kLines) * 4, th.mI - kLines * rq);
     const int vB = (cb * (int)a.ldb + kLines * kq + kLines) * 4;
-    auto load = [&](f32x4 (&x)[L], int left) {   // the chunk with `left` k to go
-        const int64_t k0 = (int64_t)a.K - left;
-#pragma unroll
-        for (int e = 0; e < PA; ++e) {
-            const auto rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(baseA + (k0 + e * PK) * a.lda), (short)0, 0x7fffffff, kRsrcWord3);
-            x[e] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rs, e * PK + ka < left ? vA : kOutside, 0, 0));
-        }
-        const auto rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(baseB + k0), (short)0, 0x7fffffff, kRsrcWord3);
-        const int vk = moved(vB, left - kLines * kq);
-#pragma unroll
-        for (int e = 0; e < PB; ++e)
-            x[PA + e] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rs, cb + CC * e < th.nJ ? vk : kOutside, e * CC * (int)a.ldb * 4, 0));
+    // pass e of the chunk with `left` k to go
+    auto load_a = [&](int left, int e) {
+        const int64_t k = (int64_t)a.K - left + e * PK;
+        const auto rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(baseA + k * a.lda), (short)0, 0x7fffffff, kRsrcWord3);
+        return __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rs, e * PK + ka < left ? vA : kOutside, 0, 0));
+    };
+    auto load_b = [&](int left, int e) {
+        const auto rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(baseB + ((int64_t)a.K - left)), (short)0, 0x7fffffff, kRsrcWord3);
+        const int v = cb + CC * e < th.nJ ? moved(vB, left - kLines * kq) : kOutside;
+        return __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rs, v, e * CC * (int)a.ldb * 4, 0));
     };
     unsigned least = 0xffffffffu;   // smallest of 2 |x| - 1 as integers, where 0 is the largest
     float sq = 0.f;
-    auto see = [&](const f32x4 (&x)[L]) {
+    auto see = [&](const f32x4& x) {
 #pragma unroll
-        for (int e = 0; e < L; ++e)
-#pragma unroll
-            for (int q = 0; q < kLines; ++q) {
-                least = min(least, (__float_as_uint(x[e][q]) << 1) - 1u);
-                sq = fmaf(x[e][q], x[e][q], sq);
-            }
+        for (int q = 0; q < kLines; ++q) {
+            least = min(least, (__float_as_uint(x[q]) << 1) - 1u);
+            sq = fmaf(x[q], x[q], sq);
+        }
     };
-    f32x4 x0[L], x1[L];
-    load(x0, a.K);
-    for (int left = a.K; left > 0; left -= 2 * CK) {
-        load(x1, left - CK);
-        see(x0);
-        load(x0, left - 2 * CK);
-        see(x1);
+    if constexpr (DEEP) {
+        f32x4 x[2][2 * P];
+        auto load = [&](f32x4 (&y)[2 * P], int left) {
+#pragma unroll
+            for (int e = 0; e < P; ++e) y[e] = load_a(left, e);
+#pragma unroll
+            for (int e = 0; e < P; ++e) y[P + e] = load_b(left, e);
+        };
+        load(x[0], a.K);
+        for (int left = a.K; left > 0; left -= 2 * CK) {
+            load(x[1], left - CK);
+#pragma unroll
+            for (int e = 0; e < 2 * P; ++e) see(x[0][e]);
+            load(x[0], left - 2 * CK);
+#pragma unroll
+            for (int e = 0; e < 2 * P; ++e) see(x[1][e]);
+        }
+    } else {
+        for (int left = a.K; left > 0; left -= CK)
+#pragma unroll 1
+            for (int e = 0; e < P; ++e) {
+                const f32x4 x = load_a(left, e), y = load_b(left, e);
+                see(x);
+                see(y);
+            }
     }
     // 2^-100; a factor of two for the sums' own rounding
-    const bool bad = least < 2 * 0x0d800000u - 1 || !(sq < kHugeNorm2 / (2 * G::NT));
+    const bool bad = (scale == 1.0f && least < 2 * 0x0d800000u - 1) || !(sq * (scale * scale) < kHugeNorm2 / (2 * G::NT));
     if (th.tid == 0) *flag = 0;
     __syncthreads();
     if (bad) *flag = 1;
@@ -175,6 +192,17 @@ __device__ __forceinline__ bool splittable(const LaunchArgs& a, const Thread& th
     __syncthreads();
     return ok;
 }
+
+// What a check asks the split tile: whether it leaves (see check in ftgemm_abft.hpp).
+template <class F, class H>
+struct Leave {
+    F norms;    // a line's norm is too large, or not finite
+    H flag;     // something is about to be logged
+    __device__ __forceinline__ bool operator()() const { return norms(); }
+    __device__ __forceinline__ bool flagged() const { return flag(); }
+};
+template <class F, class H>
+__device__ Leave(F, H) -> Leave<F, H>;
 
 // One BM x BN tile.  Returns false, with C untouched, when the tile's
 // operands do not fit the split; the caller then runs f32::tile.
@@ -217,7 +245,7 @@ __device__ __forceinline__ bool tile(const LaunchArgs& a, int tm, int tn, SmemSp
         gather_faults<G>(sm.ck, a, th);
         __syncthreads();
         faulty = __builtin_amdgcn_readfirstlane(sm.ck.nf) > 0;   // (kept unscaled, see splittable)
-        if (faulty && !splittable<G>(a, th, &sm.ck.bail)) return false;
+        if (faulty && !splittable<G, true>(a, th, &sm.ck.bail, 1.0f)) return false;
     }
     __syncthreads();
 
@@ -418,11 +446,12 @@ __device__ __forceinline__ bool tile(const LaunchArgs& a, int tm, int tn, SmemSp
     // injection hook and online check after k-step t; true: the tile leaves the split path
     int next_check = a.check_interval >= nk ? nk - 1 : a.check_interval - 1;   // (a counter: a remainder by a run-time interval is some forty instructions)
     bool checked = false;
+    bool stays = faulty;    // what the tile has logged holds: it will not leave any more
     auto post = [&](int t) -> bool {
         if constexpr (INJ) inject<G>(acc, sm.ck, a, th, t, fnext);
         checked = false;
         if constexpr (FT > 0) {
-            if (t == next_check) {
+            if (__builtin_expect(t == next_check, 0)) {
                 next_check = nk - 1 - next_check > a.check_interval ? next_check + a.check_interval : nk - 1;
                 float rr[LT], nn[LT];
 #pragma unroll
@@ -433,7 +462,13 @@ __device__ __forceinline__ bool tile(const LaunchArgs& a, int tm, int tn, SmemSp
                 const float r0 = rr[0] + rebase;
                 float ref = r0;
                 auto left = [&]() { return __builtin_amdgcn_readfirstlane(sm.ck.bail) != 0; };
-                if (check<G, FT, INJ>(acc, sm.ck, a, th, t, min((t + 1) * BK, a.K), ref, nn[0], ref, nn[0], fnext, flogged, left, unit))
+                auto flagged = [&]() {
+                    if (!stays && t + 1 < nk && !splittable<G, false>(a, opaque_lanes(th), &sm.ck.bail, scale)) return true;
+                    stays = true;
+                    return false;
+                };
+                if (check<G, FT, INJ>(acc, sm.ck, a, th, t, min((t + 1) * BK, a.K), ref, nn[0], ref, nn[0], fnext, flogged,
+                                      Leave{left, flagged}, unit))
                     return true;
                 rebase += ref - r0;
                 checked = true;

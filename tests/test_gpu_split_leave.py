@@ -116,6 +116,25 @@ def test_faults_among_large_operands_of_a_batch(h, size):
 
 
 @pytest.mark.parametrize("cfg", CONFIGS)
+@pytest.mark.parametrize("value", [np.inf, np.nan, 3e30])
+def test_events_of_a_discarded_pass(h, cfg, value):
+    """A tolerance far below roundoff flags every check; the last k of one row
+    takes its tiles off the split after two such checks.  Every check of a
+    tile has one event, and its counts are those of the events."""
+    m, n, k = 300, 270, 600
+    A, B = _operands(m, n, k, 33)
+    A[290, 597] = value
+    st, C, rep, _ = _run(h, A, B, 2, tol=1e-6, cfg=cfg)
+    keys = [(int(e["tile_m"]), int(e["tile_n"]), int(e["kstep"])) for e in rep.events]
+    assert len(keys) == len(set(keys))
+    tiles = ((m + cfg[0] - 1) // cfg[0]) * ((n + cfg[1] - 1) // cfg[1])
+    assert rep.report.checks == 3 * tiles == len(keys)      # k-steps 7, 15 and 18 of 19
+    kinds = [int(e["kind"]) for e in rep.events]
+    assert rep.report.detected == len(kinds) - kinds.count(F.EV_NONFINITE)
+    assert rep.report.uncorrectable == kinds.count(F.EV_UNCORRECTABLE)
+
+
+@pytest.mark.parametrize("cfg", CONFIGS)
 @pytest.mark.parametrize("level", [0, 1, 2])
 @pytest.mark.parametrize("ea, eb", [(-103, 30), (-106, 30), (-109, 30), (-112, 30), (-118, 36), (-125, 30), (30, -112),
                                     (-20, -90), (36, -30), (-60, -40)])
