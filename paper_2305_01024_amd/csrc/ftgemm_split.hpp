@@ -298,25 +298,26 @@ __device__ __forceinline__ bool tile(const LaunchArgs& a, int tm, int tn, SmemSp
     // ---- registers -> LDS: y[r][q] = k 4 kq + q of line r, scaled
     const float scale = INJ ? uniform(faulty ? 1.0f : kScale) : kScale, unit = INJ ? uniform(faulty ? 1.0f : kUnit) : kUnit;
     float y[LT][4];
-    // (One scalar per arm, and an asm behind it: the multiplies would otherwise be
-    // taken out of the arms, leaving a copy of every register in their place.)
-    auto transpose = [&](const f32x4 (&x)[4]) {
-        float sc = scale;
+    // A's 4 x 4 elements are transposed in place, by the wavefronts that stage it
+    // (copies, and a branch with all of it in both arms, left the matrix pipe idle
+    // for some 60 cycles a panel).
+    auto transpose = [&](f32x4 (&x)[4]) {
         if (row_role) {
-            asm volatile("; rows" : "+s"(sc));
-#pragma unroll
-            for (int r = 0; r < LT; ++r)
-#pragma unroll
-                for (int q = 0; q < 4; ++q) y[r][q] = x[q][r] * sc;
-            asm volatile("; of A" : "+v"(y[0][0]));
-        } else {
-            asm volatile("; columns" : "+s"(sc));
-#pragma unroll
-            for (int r = 0; r < LT; ++r)
-#pragma unroll
-                for (int q = 0; q < 4; ++q) y[r][q] = x[r][q] * sc;
-            asm volatile("; of B" : "+v"(y[0][0]));
+            float a01 = x[0][1], a02 = x[0][2], a03 = x[0][3], a12 = x[1][2], a13 = x[1][3], a23 = x[2][3];
+            float a10 = x[1][0], a20 = x[2][0], a30 = x[3][0], a21 = x[2][1], a31 = x[3][1], a32 = x[3][2];
+            asm volatile("v_swap_b32 %0, %6\n\tv_swap_b32 %1, %7\n\tv_swap_b32 %2, %8\n\t"
+                         "v_swap_b32 %3, %9\n\tv_swap_b32 %4, %10\n\tv_swap_b32 %5, %11"
+                         : "+v"(a01), "+v"(a02), "+v"(a03), "+v"(a12), "+v"(a13), "+v"(a23),
+                           "+v"(a10), "+v"(a20), "+v"(a30), "+v"(a21), "+v"(a31), "+v"(a32));
+            x[0][1] = a01; x[0][2] = a02; x[0][3] = a03; x[1][2] = a12; x[1][3] = a13; x[2][3] = a23;
+            x[1][0] = a10; x[2][0] = a20; x[3][0] = a30; x[2][1] = a21; x[3][1] = a31; x[3][2] = a32;
         }
+    };
+    auto scale_lines = [&](const f32x4 (&x)[4], int r0) {
+#pragma unroll
+        for (int r = r0; r < r0 + 2; ++r)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) y[r][q] = x[r][q] * scale;
     };
     constexpr int PS = BM / 32 * 64 * 8;   // halves per part
     constexpr int BUF = PARTS * PS;        // halves per panel
@@ -406,20 +407,22 @@ __device__ __forceinline__ bool tile(const LaunchArgs& a, int tm, int tn, SmemSp
         }
         __builtin_amdgcn_sched_barrier(0);
         // The vector work of the step in units, dealt out over the MFMAs
-        constexpr int FTU = FT > 0 ? LT : 0, EU = FT > 0 ? 2 : 0, U = FTU + 2 + EU + 2 * LT;
+        constexpr int FTU = FT > 0 ? LT : 0, EU = FT > 0 ? 2 : 0, U = FTU + 4 + EU + 2 * LT;
         auto unit = [&](int u) {
             if (u < FTU) {
                 ft_update(v, u);
             } else if (u == FTU) {
                 fix(x, (p + 1) * KC);
                 transpose(x);
-            } else if (u == FTU + 1) {
+            } else if (u < FTU + 3) {
+                scale_lines(x, 2 * (u - FTU - 1));
+            } else if (u == FTU + 3) {
                 load(x, p + 1 + NX);
-            } else if (u < FTU + 2 + EU) {
-                if (u == FTU + 2) encode_sum();
+            } else if (u < FTU + 4 + EU) {
+                if (u == FTU + 4) encode_sum();
                 else encode_add(buf ^ 1);
             } else {
-                const int h = u - FTU - EU - 2;
+                const int h = u - FTU - EU - 4;
                 split_half(h >> 1, h & 1);
                 if (h & 1) store_line(buf ^ 1, h >> 1);
             }
@@ -443,44 +446,61 @@ __device__ __forceinline__ bool tile(const LaunchArgs& a, int tm, int tn, SmemSp
         }
     };
 
-    // injection hook and online check after k-step t; true: the tile leaves the split path
-    int next_check = a.check_interval >= nk ? nk - 1 : a.check_interval - 1;   // (a counter: a remainder by a run-time interval is some forty instructions)
-    bool checked = false;
+    // What the k-loop stops for, after k-step t; true: the tile leaves the split.
+    // A check (every check_interval k-steps and after the last; detect-only: after
+    // the last), or without fault tolerance, where K has more than 16 k-steps, a
+    // look at the accumulators after the first 8 and after the last: operands with
+    // Inf, NaN or large elements throughout take little more than f32::tile's time,
+    // not that and the whole split's (8192^3 with one element of 1000 Inf: 12.0 ->
+    // 7.9 ms).  Detect-only has no such look, its stop would show on every call
+    // (2048^3: 118 -> 121 us): 12.9 ms.  Ends with a barrier behind the step.
     bool stays = faulty;    // what the tile has logged holds: it will not leave any more
-    auto post = [&](int t) -> bool {
-        if constexpr (INJ) inject<G>(acc, sm.ck, a, th, t, fnext);
-        checked = false;
+    auto stop = [&](int t) -> bool {
         if constexpr (FT > 0) {
-            if (__builtin_expect(t == next_check, 0)) {
-                next_check = nk - 1 - next_check > a.check_interval ? next_check + a.check_interval : nk - 1;
-                float rr[LT], nn[LT];
+            float rr[LT], nn[LT];
 #pragma unroll
-                for (int r = 0; r < LT; ++r) { rr[r] = R[r]; nn[r] = n2[r]; }
-                ReduceScatter<LT, 1, 0>::run(rr, lane);
-                ReduceScatter<LT, 1, 0>::run(nn, lane);
-                if (!(nn[0] < kHugeNorm2)) sm.ck.bail = 1;
-                const float r0 = rr[0] + rebase;
-                float ref = r0;
-                auto left = [&]() { return __builtin_amdgcn_readfirstlane(sm.ck.bail) != 0; };
-                auto flagged = [&]() {
-                    if (!stays && t + 1 < nk && !splittable<G, false>(a, opaque_lanes(th), &sm.ck.bail, scale)) return true;
-                    stays = true;
-                    return false;
-                };
-                if (check<G, FT, INJ>(acc, sm.ck, a, th, t, min((t + 1) * BK, a.K), ref, nn[0], ref, nn[0], fnext, flogged,
-                                      Leave{left, flagged}, unit))
-                    return true;
-                rebase += ref - r0;
-                checked = true;
-            }
+            for (int r = 0; r < LT; ++r) { rr[r] = R[r]; nn[r] = n2[r]; }
+            ReduceScatter<LT, 1, 0>::run(rr, lane);
+            ReduceScatter<LT, 1, 0>::run(nn, lane);
+            if (!(nn[0] < kHugeNorm2)) sm.ck.bail = 1;
+            const float r0 = rr[0] + rebase;
+            float ref = r0;
+            auto left = [&]() { return __builtin_amdgcn_readfirstlane(sm.ck.bail) != 0; };
+            auto flagged = [&]() {
+                if (!stays && t + 1 < nk && !splittable<G, false>(a, opaque_lanes(th), &sm.ck.bail, scale)) return true;
+                stays = true;
+                return false;
+            };
+            if (check<G, FT, INJ>(acc, sm.ck, a, th, t, min((t + 1) * BK, a.K), ref, nn[0], ref, nn[0], fnext, flogged,
+                                  Leave{left, flagged}, unit))
+                return true;
+            rebase += ref - r0;
+            return false;
+        } else {
+            float z = 0.f;   // stays 0 unless an accumulator is Inf or NaN
+#pragma unroll
+            for (int bi = 0; bi < MI; ++bi)
+#pragma unroll
+                for (int bj = 0; bj < NI; ++bj)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) z = fmaf(acc[bi][bj][r], 0.f, z);
+            if (!(z == 0.f) && !faulty) sm.ck.bail = 1;
+            __syncthreads();
+            return __builtin_amdgcn_readfirstlane(sm.ck.bail) != 0;
         }
-        return false;
+    };
+    const int last = nk - 1;
+    auto next_stop = [&](int t) {   // after the one behind k-step t (-1: the first)
+        if constexpr (FT > 0) return last - t > a.check_interval ? t + a.check_interval : last;
+        return t < 0 && last > 15 ? 7 : last;
     };
 
     load(xs[0], 0);
     if constexpr (NX == 2) load(xs[NX - 1], 1);
     fix(xs[0], 0);
     transpose(xs[0]);
+    scale_lines(xs[0], 0);
+    scale_lines(xs[0], 2);
     load(xs[0], NX);
 #pragma unroll
     for (int r = 0; r < LT; ++r) {
@@ -493,26 +513,16 @@ __device__ __forceinline__ bool tile(const LaunchArgs& a, int tm, int tn, SmemSp
         encode_add(0);
     }
     __syncthreads();
-    for (int t = 0; t < nk; ++t) {
-        step(2 * t, std::integral_constant<int, 0>{});
-        __syncthreads();
-        step(2 * t + 1, std::integral_constant<int, 1>{});
-        if (post(t)) return false;
-        if (!checked) __syncthreads();
-    }
-    if constexpr (FT == 0) {
-        if (!faulty) {
-            float z = 0.f;   // stays 0 unless an accumulator is Inf or NaN
-#pragma unroll
-            for (int bi = 0; bi < MI; ++bi)
-#pragma unroll
-                for (int bj = 0; bj < NI; ++bj)
-#pragma unroll
-                    for (int r = 0; r < 16; ++r) z = fmaf(acc[bi][bj][r], 0.f, z);
-            if (!(z == 0.f)) sm.ck.bail = 1;
+    for (int t = 0, at = next_stop(-1); t < nk; at = next_stop(t), ++t) {
+        for (;; ++t) {
+            step(2 * t, std::integral_constant<int, 0>{});
             __syncthreads();
-            if (__builtin_amdgcn_readfirstlane(sm.ck.bail)) return false;
+            step(2 * t + 1, std::integral_constant<int, 1>{});
+            if constexpr (INJ) inject<G>(acc, sm.ck, a, th, t, fnext);
+            if (t == at) break;
+            __syncthreads();
         }
+        if (stop(t)) return false;
     }
     // back to the product's units with alpha, unless alpha is so small that
     // the factor would be denormal
