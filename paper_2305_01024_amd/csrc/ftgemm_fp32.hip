@@ -34,12 +34,25 @@ __global__ __launch_bounds__(64 * WM * WN, (kMinWaves<BM, BN, FT>)) void ftgemm_
     }
 }
 
-// Recomputes the tiles a launch of the same variant queued (FT levels only).
+// Recomputes the tiles a launch of the same variant queued (FT levels only), on
+// the same path: a recomputed tile has the bits of one that was not flagged.
 template <int BM, int BN, int BK, int WM, int WN, int FT, bool WAVE = false>
 __global__ __launch_bounds__(64 * WM * WN) void ftgemm_f32_retry_kernel(LaunchArgs a) {
-    __shared__ f32::Smem<BM, BN, BK, WM, WN, WAVE> sm;
     const int ntm = (a.M + BM - 1) / BM;
-    abft::retry_queue(a, ntm, [&](int tm, int tn) { f32::tile<BM, BN, BK, WM, WN, FT, false, WAVE>(a, tm, tn, sm); });
+    if constexpr (kSplit<BM, BN, WAVE>) {
+        __shared__ union {
+            f32s::SmemSplit<BM, BN, WM, WN> split;
+            f32::Smem<BM, BN, BK, WM, WN> full;
+        } sm;
+        abft::retry_queue(a, ntm, [&](int tm, int tn) {
+            if (f32s::tile<BM, BN, WM, WN, FT, false>(a, tm, tn, sm.split)) return;
+            __syncthreads();
+            f32::tile<BM, BN, BK, WM, WN, FT, false>(a, tm, tn, sm.full);
+        });
+    } else {
+        __shared__ f32::Smem<BM, BN, BK, WM, WN, WAVE> sm;
+        abft::retry_queue(a, ntm, [&](int tm, int tn) { f32::tile<BM, BN, BK, WM, WN, FT, false, WAVE>(a, tm, tn, sm); });
+    }
 }
 
 __global__ void zero_u32_kernel(uint32_t* p, int n) {

@@ -194,3 +194,36 @@ def test_short_positive_sums(h, cfg, k):
     st, C, rep, _ = _run(h, A, B, 2, cfg=cfg)
     P = A.astype(np.float64) @ B.astype(np.float64)
     assert st == F.OK and np.linalg.norm(C - P) / np.linalg.norm(P) <= (np.sqrt(k / 9.0) + 1.0) * 2.0 ** -24
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16", "fp8"])
+@pytest.mark.parametrize("tile", [256, 128])
+def test_recomputed_tile_has_the_bits_of_a_clean_call(dtype, tile):
+    import torch
+    m, n, k = 300, 280, 512
+    cfg = (tile, tile, 32 if dtype == "f32" else 64, 8 if dtype == "f32" else 4)
+    g = torch.Generator(device="cuda").manual_seed(37)
+    tt = {"f32": torch.float32, "bf16": torch.bfloat16, "fp8": torch.float8_e4m3fn}[dtype]
+    dA = torch.randn((k, m), generator=g, device="cuda").to(tt)
+    dB = torch.randn((n, k), generator=g, device="cuda").to(tt)
+    handle = F.ftgemm_create({"f32": F.F32, "bf16": F.BF16, "fp8": F.F8E4M3}[dtype], 0)
+    out = []
+    try:
+        F.ftgemm_set_config(handle, cfg)
+        for faulty in (False, True):
+            dC = torch.zeros((n, m), device="cuda")
+            sites = np.zeros(4, F.FAULT_DTYPE)      # two faults in one interval of the first and the last tile
+            last_m, last_n = (m - 1) // tile, (n - 1) // tile
+            sites["tile_m"], sites["tile_n"] = (0, 0, last_m, last_m), (0, 0, last_n, last_n)
+            sites["kstep"], sites["row"], sites["col"] = (1, 2, 0, 1), (5, 20, 3, 7), (7, 17, 2, 9)
+            sites["kind"], sites["payload"] = F.FAULT_ADD, 1e5
+            F.ftgemm_set_injection(handle, sites if faulty else None)
+            rep = F.ReportBuffer(64)
+            st = F.ftgemm_run(handle, m, n, k, 1.0, dA.data_ptr(), m, dB.data_ptr(), k, 0.0, dC.data_ptr(), m,
+                              F.FT_CORRECT | F.FT_RECOMPUTE, 0.0, torch.cuda.current_stream().cuda_stream, rep)
+            assert st == F.OK and rep.report.recomputed == (2 if faulty else 0) and rep.report.recompute_failed == 0
+            out.append(dC.cpu().numpy())
+    finally:
+        F.ftgemm_set_injection(handle, None)
+        F.ftgemm_destroy(handle)
+    assert np.array_equal(out[0], out[1])
