@@ -22,7 +22,6 @@ struct ftgemm_ctx {
     ftgemm_event_t* d_events = nullptr;
     int event_cap = 0;
     uint32_t* d_counters = nullptr;
-    uint32_t* h_counters = nullptr;   // pinned copy of d_counters for the reports
     ftgemm_fault_t* d_faults = nullptr;
     int n_faults = 0, fault_cap = 0;
     ftgemm_fault_log_t* d_flog = nullptr;
@@ -305,20 +304,16 @@ bool same_plan(const ftgemm_ctx* h, int count, const ftgemm_problem_t* probs) {
 }
 
 // Counters and events of the last launch into the report.  Every count,
-// `checks` included, is taken on the device.  The copy is queued behind the
-// launch and waited for once; a wait and then a copy to pageable memory is a
-// second round trip (a reported 256^3 FP32 call 49.0 -> 40.1 us; creating a
-// handle takes 35 us more).
+// `checks` included, is taken on the device.  The copy follows the launch on its
+// stream and is the one wait; a wait and then a copy is a second round trip (a
+// reported 256^3 FP32 call 49.0 -> 39.4 us).  A stream under capture cannot be
+// waited for: the synchronisation says so, as the copy need not.
 int fill_report(const RunWorkspace& ws, hipStream_t stream, ftgemm_report_t* report, bool recompute = false) {
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(stream, &capture) != hipSuccess || capture != hipStreamCaptureStatusNone)
+        FT_HIP(hipStreamSynchronize(stream));
     uint32_t cnt[CNT_N];
-    if (ws.host_counters) {
-        FT_HIP(hipMemcpyAsync(ws.host_counters, ws.counters, sizeof(cnt), hipMemcpyDeviceToHost, stream));
-        FT_HIP(hipStreamSynchronize(stream));
-        std::memcpy(cnt, ws.host_counters, sizeof(cnt));
-    } else {
-        FT_HIP(hipStreamSynchronize(stream));
-        FT_HIP(hipMemcpy(cnt, ws.counters, sizeof(cnt), hipMemcpyDeviceToHost));
-    }
+    FT_HIP(hipMemcpyWithStream(cnt, ws.counters, sizeof(cnt), hipMemcpyDeviceToHost, stream));
     report->checks = cnt[CNT_CHECKS];
     report->detected = cnt[CNT_DETECTED];
     report->corrected = cnt[CNT_CORRECTED];
@@ -350,7 +345,6 @@ RunWorkspace workspace_of(const ftgemm_ctx* h) {
     ws.retry = h->d_retry;
     ws.retry_tiles = h->d_retry_tiles;
     ws.retry_cap = h->retry_cap;
-    ws.host_counters = h->h_counters;
     return ws;
 }
 int fill_report(ftgemm_ctx* h, hipStream_t stream, ftgemm_report_t* report, bool recompute = false) {
@@ -539,11 +533,6 @@ int ftgemm_create(ftgemm_t* handle, int dtype, int device) {
         ftgemm_destroy(h);
         return FTGEMM_NO_MEMORY;
     }
-    // without the pinned words the reports copy to pageable memory
-    if (hipHostMalloc(reinterpret_cast<void**>(&h->h_counters), sizeof(uint32_t) * CNT_N, hipHostMallocDefault) != hipSuccess) {
-        (void)hipGetLastError();
-        h->h_counters = nullptr;
-    }
     if (hipMemset(h->d_counters, 0, sizeof(uint32_t) * CNT_N) != hipSuccess ||
         hipMemset(h->d_retry, 0, sizeof(uint32_t) * 2) != hipSuccess) {
         ftgemm_destroy(h);
@@ -559,7 +548,6 @@ int ftgemm_destroy(ftgemm_t h) {
         DeviceGuard g(h->device);
         if (h->d_events) (void)hipFree(h->d_events);
         if (h->d_counters) (void)hipFree(h->d_counters);
-        if (h->h_counters) (void)hipHostFree(h->h_counters);
         if (h->d_faults) (void)hipFree(h->d_faults);
         if (h->d_flog) (void)hipFree(h->d_flog);
         if (h->d_bprobs) (void)hipFree(h->d_bprobs);

@@ -228,7 +228,6 @@ struct RunWorkspace {
     uint32_t* retry;
     int32_t* retry_tiles;
     int64_t retry_cap;
-    uint32_t* host_counters;   // CNT_N pinned words of the handle, may be null
 };
 
 // Body of ftgemm_run and ftgemm_run_noalloc on the current device (defined in
