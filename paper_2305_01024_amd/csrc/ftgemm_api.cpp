@@ -50,10 +50,12 @@ struct ftgemm_ctx {
     int grid = 0;
     bool plan_fp8 = false;   // the plan has FP8 problems: launch the kernel that holds the FP8 tile
     // cost model of the batched tile variants: multiply-adds per second, as
-    // ftgemm_tune_batched measures them (512^3), but for the FP32 64 x 64 tile:
-    // 2.7e13 there, less on sizes that divide by nothing, which it alone still
-    // loads element by element (1024 problems of 32 to 2048: 2.15 ms with 2.7e13,
-    // 2.00 ms with 2.0e13)
+    // ftgemm_tune_batched measures them (512^3), but for the FP32 64 x 64 tile,
+    // which alone still loads sizes that divide by nothing element by element:
+    // 2.7e13 at 512^3.  ms online with 1.5 / 1.8 / 2.0 / 2.7e13: 1024 problems of
+    // 32 to 2048 1.81 / 1.87 / 1.89 / 1.92 and, of other sizes, 1.55 / 1.55 / 1.60 /
+    // 1.61; 300 of them 0.45 / 0.58 / 0.59 / 0.58; 1024 of 32 to 256 0.079 / 0.078 /
+    // 0.081 / 0.095; 16 of 32 to 2048 0.045 / 0.045 / 0.044 / 0.045
     double batch_rate[kBatchVariants] = {6.4e13, 1.8e13, 1.07e14, 1.19e14};
 };
 
@@ -122,13 +124,14 @@ bool dtype_supported(int dtype) {
 // has its SIMD to itself runs faster, not proportionally: a 128x128
 // workgroup alone on a compute unit takes ~0.65 of the time it takes beside
 // another); a 64x64 workgroup is one wavefront, so a partial wave of it
-// still takes a full wave's time.
+// still takes a full wave's time.  A variant that is kept against larger ones
+// (keep_ft) is given that much less.
 double modelled_time(const Variant& x, const VariantModel& mdl, int64_t m, int64_t n, bool ft) {
     constexpr double kPartialWave = 0.65;
     constexpr int kSimdsPerCU = 4;
     const int64_t tiles = ((m + x.m_tile - 1) / x.m_tile) * ((n + x.n_tile - 1) / x.n_tile);
     const int64_t slots = (int64_t)kNumCUs * mdl.wg_per_cu;
-    const double wave = (double)slots * x.m_tile * x.n_tile / (ft ? mdl.tflops_ft : mdl.tflops_plain);
+    const double wave = (double)slots * x.m_tile * x.n_tile / (ft ? mdl.tflops_ft * mdl.keep_ft : mdl.tflops_plain);
     const int64_t full = tiles / slots, rem = tiles - full * slots;
     double t = (double)full * wave;
     if (rem > 0) {

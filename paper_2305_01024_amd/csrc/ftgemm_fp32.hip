@@ -87,14 +87,14 @@ constexpr Variant kVariants[] = {
 };
 constexpr int kNumVariants = sizeof(kVariants) / sizeof(kVariants[0]);
 // aligned with kVariants (the wavefront-check variant is never auto-selected).
-// Online, 128 x 128 runs at 159 TFLOP/s when all compute units are full; it is
-// weighted as 193 because the compute tile is also the check tile, the unit in
-// which a call reports and corrects, and the automatic one stays the finer one
-// where it was: 256 x 256 from 3584 on except near 5120 and 6144 (ms online,
-// 256 / 128: 2560 0.335 / 0.260, 3072 0.394 / 0.476, 3584 0.504 / 0.690, 5120
-// 1.460 / 1.798, 6144 2.790 / 2.840; ftgemm_tune picks the faster).
+// The compute tile is also the check tile, the unit in which a call reports and
+// corrects, so at the FT levels the 128 x 128 tile is kept until a larger one is
+// 193/159 = 1.21 times as fast: 256 x 256 from 3584 on except near 5120 and 6144,
+// as before the split kernels (ms online, 256 / 128: 2560 0.335 / 0.260, 3072
+// 0.394 / 0.476, 3584 0.504 / 0.690, 5120 1.460 / 1.798, 6144 2.790 / 2.840;
+// ftgemm_tune picks the faster).
 constexpr VariantModel kModels[] = {
-    {1, 8, 224.0f, 210.5f}, {1, 4, 123.0f, 105.5f}, {1, 4, 124.0f, 101.0f}, {2, 4, 186.0f, 193.0f},
+    {1, 8, 224.0f, 210.5f}, {1, 4, 123.0f, 105.5f}, {1, 4, 124.0f, 101.0f}, {2, 4, 186.0f, 159.0f, 193.0f / 159.0f},
     {4, 1, 115.0f, 83.7f}, {2, 4, 186.0f, 96.2f},
 };
 static_assert(sizeof(kModels) / sizeof(kModels[0]) == kNumVariants, "one model entry per variant");

@@ -67,10 +67,12 @@ Variant fp32_variant(int idx);
 // Default-selection cost model of an FP32 variant: workgroups resident per
 // compute unit, wavefronts per workgroup, and the throughput (TFLOP/s) of its
 // plain and online FT kernels with every compute unit full (measured on
-// MI355X at 8192^3).
+// MI355X at 8192^3).  keep_ft: how much faster a larger tile has to be modelled
+// before it is taken in this one's place at the FT levels.
 struct VariantModel {
     int wg_per_cu, waves_per_wg;
     float tflops_plain, tflops_ft;
+    float keep_ft = 1.0f;
 };
 VariantModel fp32_variant_model(int idx);
 int fp32_find_variant(int m_tile, int n_tile, int k_step, int check_m, int check_n);
