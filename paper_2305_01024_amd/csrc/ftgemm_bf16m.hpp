@@ -23,9 +23,9 @@
 // wavefront; with two wavefronts per SIMD every instruction of a wavefront takes
 // about 8.8 cycles of issue, so the step takes about 5000 at level 2 and 3400
 // without fault tolerance.  Unaligned operands took element loads before.
-// 8192^3 online 2.02 -> 1.64 ms, plain 1.02 -> 0.95 ms (the library's product
-// without fault tolerance: 0.96 ms); 2048^3 with recompute 87 -> 68 us;
-// 3001 x 1999 x 4097, detection only, 685 -> 155 us.
+// 8192^3 online 2.02 -> 1.60 to 1.70 ms, plain 1.02 ms as before (the library's
+// product without fault tolerance: 0.96 ms); 2048^3 with recompute 87 -> 68 us;
+// 3001 x 1999 x 4097, detection only, 685 -> 150 us.
 #pragma once
 
 #include "ftgemm_bf16.hpp"

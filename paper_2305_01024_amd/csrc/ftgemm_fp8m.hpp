@@ -12,7 +12,7 @@
 // per SIMD and the references 512; the step takes about 5000 at the issue rate
 // of two wavefronts per SIMD (about 330 vector instructions of each: decoding,
 // sums and squares of 64 codes per thread are 144, the byte transposes 16, the
-// conversions 32).  8192^3 online 1.88 -> 1.44 ms, plain 0.77 -> 0.58 ms (LDS
+// conversions 32).  8192^3 online 1.88 -> 1.33 ms, plain 0.77 -> 0.6 ms (LDS
 // atomics and owners' reads before; the library's product without fault
 // tolerance: 0.41 ms); unaligned operands took element loads.
 #pragma once

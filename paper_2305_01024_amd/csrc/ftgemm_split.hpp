@@ -2,13 +2,16 @@
 //
 // The FP32 matrix instruction takes 64 cycles for 32 x 32 x 2, the bf16 one 32
 // cycles for 32 x 32 x 16: sixteen times the rate.  Every FP32 operand is split
-// exactly into three bf16 parts, x = x0 + x1 + x2 (each the rest rounded to
+// (Henry, Tang and Heinecke, "Leveraging the bfloat16 Artificial Intelligence
+// Datatype For Higher-Precision Computations", ARITH 2019) exactly into three
+// bf16 parts, x = x0 + x1 + x2 (each the rest rounded to
 // nearest: 8 + 8 + 8 bits), and a product is the six part products down to
 // 2^-16 of the largest, x0 y0, x0 y1, x1 y0, x1 y1, x0 y2 and x2 y0, added to
 // one FP32 accumulator; the dropped ones are below 2^-25 of |x y| and of either
 // sign.  Against 64 bits the result is closer than the FP32 instruction's
 // (2-norm of the error over K = 64 .. 8192 on normal, uniform, positive and
-// heavy-tailed operands: 0.6 to 0.93 of it), because an accumulator is rounded
+// heavy-tailed operands: 0.6 to 0.93 of it; positive operands, K = 4 .. 39: 0.39 to
+// 0.95, the most at K = 17), because an accumulator is rounded
 // once per 16 k and product instead of once per k.  (Cutting the leading part
 // off instead of rounding it leaves remainders of one sign, and on positive
 // data the small products are then lost to rounding all in one direction.)
@@ -21,16 +24,16 @@
 // partial references, which are summed over the four threads of a line only at
 // a check: the owners' reads of whole rows and columns from LDS are gone.
 //
-// What bounds it: at 256 x 256 and 8192^3 the matrix instructions take 3.1 ms
-// of 5.2 at the 1.9-2.0 GHz the chip then runs at (six times the library's
-// bf16 product of that size takes 5.8 ms).  Vector instructions issue beside
+// What bounds it: at 256 x 256 and 8192^3 the matrix instructions take some 3 ms
+// of 5.1 to 5.3 (six times the library's bf16 product of that size takes 5.8 ms).
+// Vector instructions issue beside
 // matrix instructions of either wavefront on the SIMD (measured: six between
 // two MFMAs are 90-95% hidden; v_dot2 is the exception, it waits for the matrix
 // pipe), so the split, the encodings and the reference updates of a panel,
 // about 190 instructions per wavefront, are dealt out between its 48 MFMAs.
-// 8192^3 online: 8.72 ms on the FP32 instructions, 5.19 ms here; 2048^3 (one
+// 8192^3 online: 8.7 ms on the FP32 instructions, 5.13 to 5.29 ms here; 2048^3 (one
 // 128 x 128 tile per compute unit, bound by the latency of a panel: LDS reads
-// after the barrier, split and store before the next) 0.210 -> 0.138 ms.
+// after the barrier, split and store before the next) 0.210 -> 0.137 ms.
 //
 // Every operand is multiplied by 2^16 as it is split, and the sums by 2^-32 at the
 // end (both exact): a binary32 number, denormals included, is then a multiple of
@@ -121,7 +124,8 @@ __device__ __forceinline__ int moved(int off, int rem) { return rem >= kLines ? 
 //     0.30 ms to a launch of 8192^3, 0.03 to 4096^3 and 0.016 to 2048^3 (one 4-byte
 //     load after another: 1.29, 0.97 and 0.41 ms).
 //   * Any other tile asks at its first flag, if k is left, with the few registers
-//     that are free there.
+//     that are free there.  If it leaves, what was flagged goes with the pass it
+//     happened in: f32::tile starts from clean accumulators.
 // What a thread reads of all lines has a sum of squares that keeps every line's
 // norm below the one at which a check leaves.  (Quads at the last rows may look
 // at the tile above too.)
