@@ -5,6 +5,7 @@
 #include <cmath>
 #include <cstdlib>
 #include <cstring>
+#include <mutex>
 #include <new>
 #include <string>
 #include <vector>
@@ -22,6 +23,7 @@ struct ftgemm_ctx {
     ftgemm_event_t* d_events = nullptr;
     int event_cap = 0;
     uint32_t* d_counters = nullptr;
+    uint32_t* h_counters = nullptr;   // the handle's words of the shared page (ReportWords), may be null
     ftgemm_fault_t* d_faults = nullptr;
     int n_faults = 0, fault_cap = 0;
     ftgemm_fault_log_t* d_flog = nullptr;
@@ -306,17 +308,59 @@ bool same_plan(const ftgemm_ctx* h, int count, const ftgemm_problem_t* probs) {
            (count == 0 || std::memcmp(h->plan_probs.data(), probs, sizeof(ftgemm_problem_t) * (size_t)count) == 0);
 }
 
+// Pinned words that the counters of a report are copied to: one page, shared by
+// the process's handles, 64 bytes each.  The first handle allocates it and the
+// last gives it back; a handle that finds no room goes without.  (An
+// allocation per handle took 11 to 25 us of creating each.)
+struct ReportWords {
+    static constexpr int kSlots = 64, kWords = 16;
+    static_assert(CNT_N <= kWords, "a slot holds the counters");
+    std::mutex mu;
+    uint32_t* page = nullptr;
+    uint64_t used = 0;
+
+    uint32_t* take() {
+        std::lock_guard<std::mutex> lock(mu);
+        if (!page && hipHostMalloc(reinterpret_cast<void**>(&page), sizeof(uint32_t) * kSlots * kWords, hipHostMallocPortable) != hipSuccess) {
+            (void)hipGetLastError();
+            page = nullptr;
+        }
+        if (!page || used == ~uint64_t(0)) return nullptr;
+        const int q = __builtin_ctzll(~used);
+        used |= uint64_t(1) << q;
+        return page + q * kWords;
+    }
+    void give(uint32_t* words) {
+        if (!words) return;
+        std::lock_guard<std::mutex> lock(mu);
+        used &= ~(uint64_t(1) << ((words - page) / kWords));
+        if (used == 0) {
+            (void)hipHostFree(page);
+            page = nullptr;
+        }
+    }
+};
+ReportWords g_report_words;
+
 // Counters and events of the last launch into the report.  Every count,
 // `checks` included, is taken on the device.  The copy follows the launch on its
-// stream and is the one wait; a wait and then a copy is a second round trip (a
-// reported 256^3 FP32 call 49.0 -> 39.4 us).  A stream under capture cannot be
-// waited for: the synchronisation says so, as the copy need not.
+// stream and there is one wait; a wait and then a copy is a second round trip (a
+// reported 256^3 FP32 call 49.0 -> 39.4 us).  Without pinned words the copy
+// itself waits, and a synchronisation after it takes some 6 us more; a stream under
+// capture cannot be waited for, which the synchronisation says and the copy
+// need not.
 int fill_report(const RunWorkspace& ws, hipStream_t stream, ftgemm_report_t* report, bool recompute = false) {
-    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(stream, &capture) != hipSuccess || capture != hipStreamCaptureStatusNone)
-        FT_HIP(hipStreamSynchronize(stream));
     uint32_t cnt[CNT_N];
-    FT_HIP(hipMemcpyWithStream(cnt, ws.counters, sizeof(cnt), hipMemcpyDeviceToHost, stream));
+    if (ws.host_counters) {
+        FT_HIP(hipMemcpyAsync(ws.host_counters, ws.counters, sizeof(cnt), hipMemcpyDeviceToHost, stream));
+        FT_HIP(hipStreamSynchronize(stream));
+        std::memcpy(cnt, ws.host_counters, sizeof(cnt));
+    } else {
+        hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+        if (hipStreamIsCapturing(stream, &capture) != hipSuccess || capture != hipStreamCaptureStatusNone)
+            FT_HIP(hipStreamSynchronize(stream));
+        FT_HIP(hipMemcpyWithStream(cnt, ws.counters, sizeof(cnt), hipMemcpyDeviceToHost, stream));
+    }
     report->checks = cnt[CNT_CHECKS];
     report->detected = cnt[CNT_DETECTED];
     report->corrected = cnt[CNT_CORRECTED];
@@ -348,6 +392,7 @@ RunWorkspace workspace_of(const ftgemm_ctx* h) {
     ws.retry = h->d_retry;
     ws.retry_tiles = h->d_retry_tiles;
     ws.retry_cap = h->retry_cap;
+    ws.host_counters = h->h_counters;
     return ws;
 }
 int fill_report(ftgemm_ctx* h, hipStream_t stream, ftgemm_report_t* report, bool recompute = false) {
@@ -536,6 +581,7 @@ int ftgemm_create(ftgemm_t* handle, int dtype, int device) {
         ftgemm_destroy(h);
         return FTGEMM_NO_MEMORY;
     }
+    h->h_counters = g_report_words.take();
     if (hipMemset(h->d_counters, 0, sizeof(uint32_t) * CNT_N) != hipSuccess ||
         hipMemset(h->d_retry, 0, sizeof(uint32_t) * 2) != hipSuccess) {
         ftgemm_destroy(h);
@@ -551,6 +597,7 @@ int ftgemm_destroy(ftgemm_t h) {
         DeviceGuard g(h->device);
         if (h->d_events) (void)hipFree(h->d_events);
         if (h->d_counters) (void)hipFree(h->d_counters);
+        g_report_words.give(h->h_counters);
         if (h->d_faults) (void)hipFree(h->d_faults);
         if (h->d_flog) (void)hipFree(h->d_flog);
         if (h->d_bprobs) (void)hipFree(h->d_bprobs);

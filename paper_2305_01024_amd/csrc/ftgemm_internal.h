@@ -230,6 +230,7 @@ struct RunWorkspace {
     uint32_t* retry;
     int32_t* retry_tiles;
     int64_t retry_cap;
+    uint32_t* host_counters;   // CNT_N pinned words of a handle, may be null
 };
 
 // Body of ftgemm_run and ftgemm_run_noalloc on the current device (defined in
