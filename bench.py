@@ -758,7 +758,7 @@ def _offline_model(tiles, t_plain, t_det, t_online, t_retry_extra, q, gamma0=1.0
     gamma = 1.0 - (1.0 - gamma0) ** tiles
     runs = (1.0 - gamma) / (1.0 - 2.0 * gamma) if gamma < 0.5 else None
     r = t_online / t_det
-    gamma_star = (r - 1.0) / (2.0 * r - 1.0)
+    gamma_star = max(0.0, (r - 1.0) / (2.0 * r - 1.0))   # online no slower than detect-only: at every rate
     gamma0_star = 1.0 - (1.0 - gamma_star) ** (1.0 / tiles)
     return {"tiles": int(tiles), "gamma0": gamma0, "gamma": round(gamma, 6),
             "offline_expected_runs": round(runs, 4) if runs is not None else "unbounded (gamma >= 1/2)",
