@@ -281,9 +281,14 @@ __device__ __forceinline__ bool tile(const LaunchArgs& a, int tm, int tn, SmemSp
         for (int e = 0; e < 4; ++e) x[e] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rs, vo[e], e * estride, 0));
     };
     const int shift = (LT - (row_role ? mI : a.K) % LT) % LT;
-    auto fix = [&](f32x4 (&x)[4], int k0) {
-        if (shift == 0 || (!row_role && (k0 >= a.K || k0 + KC <= a.K))) return;
-        const int rem = row_role ? mI - LT * lq : a.K - (k0 + 4 * kq);
+    // The panels to fix are those p with (p & fix_mask) == fix_panel: every one of
+    // rows that are cut, the one of columns in which K ends, or none.  (One test:
+    // the three branches of the conditions written out cost every panel of a
+    // ragged tile; 7040 x 128 x 910 online 63.4 -> 58.9 us.)
+    const int fix_mask = shift != 0 && !row_role ? ~0 : 0, fix_panel = shift == 0 ? 1 : row_role ? 0 : a.K / KC;
+    auto fix = [&](f32x4 (&x)[4], int p) {
+        if ((p & fix_mask) != fix_panel) return;
+        const int rem = row_role ? mI - LT * lq : a.K - (p * KC + 4 * kq);
         const bool cut = rem > 0 && rem < LT;
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
@@ -416,7 +421,7 @@ __device__ __forceinline__ bool tile(const LaunchArgs& a, int tm, int tn, SmemSp
             if (u < FTU) {
                 ft_update(v, u);
             } else if (u == FTU) {
-                fix(x, (p + 1) * KC);
+                fix(x, p + 1);
                 transpose(x);
             } else if (u < FTU + 3) {
                 scale_lines(x, 2 * (u - FTU - 1));
