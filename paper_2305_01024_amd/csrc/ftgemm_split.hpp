@@ -33,7 +33,7 @@
 // about 190 instructions per wavefront, are dealt out between its 48 MFMAs.
 // 8192^3 online: 8.7 ms on the FP32 instructions, 5.13 to 5.29 ms here; 2048^3 (one
 // 128 x 128 tile per compute unit, bound by the latency of a panel: LDS reads
-// after the barrier, split and store before the next) 0.210 -> 0.137 ms.
+// after the barrier, split and store before the next) 0.210 -> 0.131 ms.
 //
 // Every operand is multiplied by 2^16 as it is split, and the sums by 2^-32 at the
 // end (both exact): a binary32 number, denormals included, is then a multiple of
